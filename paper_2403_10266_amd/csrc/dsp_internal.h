@@ -131,7 +131,7 @@ int launch_layernorm_bwd(const void* x, int x_bf16, const void* dy, int dy_bf16,
                          int64_t rows, int C, float eps, hipStream_t s, RowSwap rs = RowSwap(),
                          void* dx2 = nullptr, int dx2_bf16 = 0);
 
-// out = epilogue(a W^T + bias) (gemm.hip).  pre (GELU or ReLU epilogue only,
+// out = epilogue(a W^T + bias) (gemm.hip; fp32: gemm_f32.hip).  pre (GELU or ReLU epilogue only,
 // else null): also receives the pre-activation, in the output's dtype.  rs:
 // output rows permuted as above (the residual is read in the input's order).
 int launch_linear_bf16(const void* a, const void* w, const void* bias, const float* residual,

@@ -19,7 +19,7 @@
 //    pre-activation (or GELU' there), and the activation's backward (the sum
 //    times act'(u), or times a kept GELU').
 //  * A batched bf16 transpose for the block backward's weights.
-// fp32 path: LDS-tiled FMA kernel, 64 x 64 tile, 4 x 4 outputs per thread.
+// The fp32 path is in gemm_f32.hip.
 #include <math.h>
 
 #include <type_traits>
@@ -689,74 +689,6 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_bf16_big_kernel(
   }
 }
 
-// ---------------------------------------------------------------- fp32 path
-constexpr int FT = 64, FK = 64;  // one global round trip per 64-wide K slice
-
-// `pre` (GELU/ReLU, may be null): also store the pre-activation there.
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A,
-                                                        const float* __restrict__ W,
-                                                        const float* __restrict__ bias,
-                                                        const float* resid, float* out, float* pre,
-                                                        int M, int N, int K, RowSwap rs) {
-  __shared__ float As[FK][FT + 1];
-  __shared__ float Bs[FK][FT + 1];
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += FK) {
-    // all loads of the slice first (one round trip), then the LDS stores
-    constexpr int PER = FT * FK / 256;
-    float la[PER], lb[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = threadIdx.x + 256 * i;
-      const int r = e / FK, kk = e % FK;
-      const int gm = m0 + r, gn = n0 + r, gk = k0 + kk;
-      la[i] = (gm < M && gk < K) ? A[(int64_t)gm * K + gk] : 0.0f;
-      lb[i] = (gn < N && gk < K) ? W[(int64_t)gn * K + gk] : 0.0f;
-    }
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = threadIdx.x + 256 * i;
-      As[e % FK][e / FK] = la[i];
-      Bs[e % FK][e / FK] = lb[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < FK; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty + 16 * i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx + 16 * j;
-      if (n >= N) continue;
-      float v = acc[i][j];
-      if (bias) v += bias[n];
-      const int64_t off = rs.map(m) * N + n;
-      if ((EPI == DSP_EPI_GELU || EPI == DSP_EPI_RELU) && pre) pre[off] = v;
-      if (EPI == DSP_EPI_GELU) v = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
-      if (EPI == DSP_EPI_RELU) v = fmaxf(v, 0.0f);
-      if (EPI == DSP_EPI_RESID) v += resid[(int64_t)m * N + n];
-      out[off] = v;
-    }
-  }
-}
-
 // bf16 transposes of up to kMaxTranspose matrices in one launch (the weights
 // of the block backward), one 64 x 64 tile per work-group: 16-byte chunks of
 // 8 elements in, through LDS, 16-byte chunks out.  Rows and columns are
@@ -882,28 +814,6 @@ int launch_linear_bf16(const void* a, const void* w, const void* bias, const flo
     case DSP_EPI_GELU_BWD: DSP_GEMM_LAUNCH(DSP_EPI_GELU_BWD, false); break;
     case DSP_EPI_SCALE_BWD: DSP_GEMM_LAUNCH(DSP_EPI_SCALE_BWD, false); break;
     case DSP_EPI_RELU_BWD: DSP_GEMM_LAUNCH(DSP_EPI_RELU_BWD, false); break;
-    default:
-      return DSP_ERR_ARG;
-  }
-#undef DSP_GEMM_LAUNCH
-  return last_launch_status();
-}
-
-int launch_linear_f32(const float* a, const float* w, const float* bias, const float* residual,
-                      float* out, int64_t M, int N, int K, int epilogue, hipStream_t s, float* pre, RowSwap rs) {
-  if (M == 0) return DSP_OK;
-  const int64_t gy = (M + FT - 1) / FT;
-  if (gy >= 65536 * 1024) return DSP_ERR_SHAPE;
-  if (pre && epilogue != DSP_EPI_GELU && epilogue != DSP_EPI_RELU) return DSP_ERR_ARG;
-  const dim3 grid((uint32_t)((N + FT - 1) / FT), (uint32_t)gy), block(256);
-#define DSP_GEMM_LAUNCH(E) \
-  hipLaunchKernelGGL(gemm_f32_kernel<E>, grid, block, 0, s, a, w, bias, residual, out, pre, (int)M, N, K, rs)
-  switch (epilogue) {
-    case DSP_EPI_NONE: DSP_GEMM_LAUNCH(DSP_EPI_NONE); break;
-    case DSP_EPI_GELU: DSP_GEMM_LAUNCH(DSP_EPI_GELU); break;
-    case DSP_EPI_RESID: DSP_GEMM_LAUNCH(DSP_EPI_RESID); break;
-    case DSP_EPI_F32: DSP_GEMM_LAUNCH(DSP_EPI_NONE); break;
-    case DSP_EPI_RELU: DSP_GEMM_LAUNCH(DSP_EPI_RELU); break;
     default:
       return DSP_ERR_ARG;
   }

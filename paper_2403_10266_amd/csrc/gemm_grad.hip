@@ -565,29 +565,6 @@ int launch_grad(const GradArgs& p0, int splits, float* ws, hipStream_t s) {
   return last_launch_status();
 }
 
-// fp32 path: out[m][n] = sum_k A(m, k) B(n, k) with the same storage choices,
-// plain FMA, one thread per output (small problems and checks)
-__global__ __launch_bounds__(256) void gemm_grad_f32_kernel(const float* a, int ta, int64_t lda, const float* b,
-                                                            int tb, int64_t ldb, const float* aux, float* out,
-                                                            int64_t M, int64_t N, int64_t K, int epi) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= M * N) return;
-  const int64_t m = i / N, n = i % N;
-  float s = 0.0f;
-  for (int64_t k = 0; k < K; ++k) {
-    const float av = ta ? a[k * lda + m] : a[m * lda + k];
-    const float bv = tb ? b[k * ldb + n] : b[n * ldb + k];
-    s = fmaf(av, bv, s);
-  }
-  if (epi == DSP_GRAD_EPI_GELU_BWD) {
-    const float u = aux[i];
-    s *= 0.5f * (1.0f + erff(u * 0.70710678118654752f)) + u * 0.3989422804014327f * expf(-0.5f * u * u);
-  } else if (epi == DSP_GRAD_EPI_RELU_BWD) {
-    s = aux[i] > 0.0f ? s : 0.0f;
-  }
-  out[i] = s;
-}
-
 // out = a + b (fp32); out may alias a or b
 __global__ __launch_bounds__(256) void add_f32_kernel(const float* a, const float* b, float* out, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -600,17 +577,6 @@ int launch_add_f32(const float* a, const float* b, float* out, int64_t n, hipStr
   if (n == 0) return DSP_OK;
   const int64_t blocks = std::min<int64_t>((n + 255) / 256, 65536);
   hipLaunchKernelGGL(add_f32_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, a, b, out, n);
-  return last_launch_status();
-}
-
-int launch_gemm_grad_f32(const float* a, int ta, int64_t lda, const float* b, int tb, int64_t ldb,
-                         const float* aux, float* out, int64_t M, int64_t N, int64_t K, int epi, hipStream_t s) {
-  const int64_t total = M * N;
-  if (total == 0) return DSP_OK;
-  const int64_t blocks = (total + 255) / 256;
-  if (blocks >= (int64_t(1) << 31)) return DSP_ERR_SHAPE;
-  hipLaunchKernelGGL(gemm_grad_f32_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, a, ta, lda, b, tb, ldb, aux,
-                     out, M, N, K, epi);
   return last_launch_status();
 }
 
