@@ -877,104 +877,6 @@ __global__ __launch_bounds__(NW * 128, 1) void attn_bwd_short_kernel(BwdParams p
   }
 }
 
-// ---------------------------------------------------------------------------
-// fp32 path: plain FMA loops.  One thread per (unit, row, 32-column slice):
-// the dQ kernel's units are query heads (rows: queries), the dK/dV kernel's
-// key/value heads (rows: keys; it visits every query head of the group).
-constexpr int DC = 32;
-
-struct BwdParamsF {
-  const float* q;
-  const float* k;
-  const float* v;
-  const float* o;
-  const float* dout;
-  const float* lse;
-  float* dq;
-  float* dk;
-  float* dv;
-  float* delta;
-  int64_t b_q, x_q, r_q, b_kv, x_kv, r_kv, b_o, x_o, r_o;
-  int64_t X, H, L, Lk, grp, D, n_dc;
-  float scale;
-};
-
-__device__ __forceinline__ float dotf(const float* a, const float* b, int64_t n) {
-  float s = 0.0f;
-  for (int64_t d = 0; d < n; ++d) s = fmaf(a[d], b[d], s);
-  return s;
-}
-
-__global__ __launch_bounds__(256) void attn_bwd_f32_dq_kernel(BwdParamsF p, int64_t total) {
-  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= total) return;
-  const int64_t c0 = (tid % p.n_dc) * DC, ur = tid / p.n_dc;
-  const int64_t nc = min((int64_t)DC, p.D - c0);
-  const int64_t row = ur % p.L, unit = ur / p.L;
-  const int64_t h = unit % p.H, bx = unit / p.H, xx = bx % p.X, bb = bx / p.X;
-  const float* qrow = p.q + bb * p.b_q + xx * p.x_q + h * p.D + row * p.r_q;
-  const int64_t ob = bb * p.b_o + xx * p.x_o + h * p.D + row * p.r_o;
-  const int64_t kvb = bb * p.b_kv + xx * p.x_kv + (h / p.grp) * p.D;
-  const float* drow = p.dout + ob;
-  const float delta = dotf(drow, p.o + ob, p.D);
-  const float lse = p.lse[unit * p.L + row];
-  if (c0 == 0) p.delta[unit * p.L + row] = delta;
-  float acc[DC];
-#pragma unroll
-  for (int c = 0; c < DC; ++c) acc[c] = 0.0f;
-  for (int64_t j = 0; j < p.Lk; ++j) {
-    const float* krow = p.k + kvb + j * p.r_kv;
-    const float pr = expf(dotf(qrow, krow, p.D) * p.scale - lse);
-    const float dz = pr * (dotf(drow, p.v + kvb + j * p.r_kv, p.D) - delta);
-#pragma unroll
-    for (int c = 0; c < DC; ++c)
-      if (c < nc) acc[c] = fmaf(dz, krow[c0 + c], acc[c]);
-  }
-  float* out = p.dq + bb * p.b_q + xx * p.x_q + h * p.D + row * p.r_q + c0;
-#pragma unroll
-  for (int c = 0; c < DC; ++c)
-    if (c < nc) out[c] = acc[c] * p.scale;
-}
-
-__global__ __launch_bounds__(256) void attn_bwd_f32_dkv_kernel(BwdParamsF p, int64_t total) {
-  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= total) return;
-  const int64_t Hkv = p.H / p.grp;
-  const int64_t c0 = (tid % p.n_dc) * DC, ur = tid / p.n_dc;
-  const int64_t nc = min((int64_t)DC, p.D - c0);
-  const int64_t key = ur % p.Lk, unit = ur / p.Lk;
-  const int64_t hk = unit % Hkv, bx = unit / Hkv, xx = bx % p.X, bb = bx / p.X;
-  const int64_t kvb = bb * p.b_kv + xx * p.x_kv + hk * p.D + key * p.r_kv;
-  const float* krow = p.k + kvb;
-  const float* vrow = p.v + kvb;
-  float ak[DC], av[DC];
-#pragma unroll
-  for (int c = 0; c < DC; ++c) ak[c] = av[c] = 0.0f;
-  for (int64_t hq = hk * p.grp; hq < (hk + 1) * p.grp; ++hq) {
-    const int64_t uq = bx * p.H + hq;
-    for (int64_t i = 0; i < p.L; ++i) {
-      const float* qrow = p.q + bb * p.b_q + xx * p.x_q + hq * p.D + i * p.r_q;
-      const float* drow = p.dout + bb * p.b_o + xx * p.x_o + hq * p.D + i * p.r_o;
-      const float pr = expf(dotf(qrow, krow, p.D) * p.scale - p.lse[uq * p.L + i]);
-      const float dz = pr * (dotf(drow, vrow, p.D) - p.delta[uq * p.L + i]);
-#pragma unroll
-      for (int c = 0; c < DC; ++c)
-        if (c < nc) {
-          ak[c] = fmaf(dz, qrow[c0 + c], ak[c]);
-          av[c] = fmaf(pr, drow[c0 + c], av[c]);
-        }
-    }
-  }
-  float* ok = p.dk + kvb + c0;
-  float* ov = p.dv + kvb + c0;
-#pragma unroll
-  for (int c = 0; c < DC; ++c)
-    if (c < nc) {
-      ok[c] = ak[c] * p.scale;
-      ov[c] = av[c];
-    }
-}
-
 template <typename P>
 void fill_common(P& p, const AttnBwdArgs& a) {
   p.b_q = a.q_strides[0];
@@ -1105,35 +1007,6 @@ int launch_attn_bwd_bf16(const AttnBwdArgs& a, hipStream_t s) {
     case 96: return launch_bwd_d<96>(a, s);
     default: return DSP_ERR_SHAPE;
   }
-}
-
-int launch_attn_bwd_f32(const AttnBwdArgs& a, hipStream_t s) {
-  BwdParamsF p;
-  p.q = static_cast<const float*>(a.q);
-  p.k = static_cast<const float*>(a.k);
-  p.v = static_cast<const float*>(a.v);
-  p.o = static_cast<const float*>(a.o);
-  p.dout = static_cast<const float*>(a.dout);
-  p.dq = static_cast<float*>(a.dq);
-  p.dk = static_cast<float*>(a.dk);
-  p.dv = static_cast<float*>(a.dv);
-  fill_common(p, a);
-  p.X = a.X;
-  p.H = a.H;
-  p.L = a.L;
-  p.Lk = a.Lk;
-  p.grp = a.H / a.Hkv;
-  p.D = a.D;
-  p.n_dc = (a.D + DC - 1) / DC;
-  p.scale = a.scale;
-  const int64_t tq = a.B * a.X * a.H * a.L * p.n_dc, tk = a.B * a.X * a.Hkv * a.Lk * p.n_dc;
-  if (tq == 0) return DSP_OK;
-  if ((tq + 255) / 256 >= (int64_t(1) << 31) || (tk + 255) / 256 >= (int64_t(1) << 31)) return DSP_ERR_SHAPE;
-  hipLaunchKernelGGL(attn_bwd_f32_dq_kernel, dim3((uint32_t)((tq + 255) / 256)), dim3(256), 0, s, p, tq);
-  int st = last_launch_status();
-  if (st != DSP_OK || tk == 0) return st;
-  hipLaunchKernelGGL(attn_bwd_f32_dkv_kernel, dim3((uint32_t)((tk + 255) / 256)), dim3(256), 0, s, p, tk);
-  return last_launch_status();
 }
 
 }  // namespace dsp
