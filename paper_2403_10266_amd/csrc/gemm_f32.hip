@@ -11,8 +11,9 @@
 // the tile.  What does is having several waves on every SIMD at the few thousand
 // rows that fp32 runs have: 4 waves on a 64 x 64 tile (each a quarter), K in slices
 // of 32 through two LDS buffers with one barrier per slice, the next slice's
-// global loads issued before the current one's MFMAs.  (128 x 128 tiles: 77 against
-// 92 TFLOP/s at 4096 x 3456 x 1152, 32 against 64 at 2048 x 1152 x 1152.)
+// global loads issued during the current one's MFMAs.  (128 x 128 tiles: 77
+// against 92 TFLOP/s at 4096 x 3456 x 1152 and 32 against 64 at 2048 x 1152 x 1152,
+// both with masked loads.)
 //  * Few tiles: KS groups of 4 waves share a tile, each with 1 / KS of the
 //    reduction and buffers of its own, and group 0 adds the partial sums in order
 //    (deterministic, no workspace).  Alone on its SIMD a wave waits for every
@@ -24,9 +25,10 @@
 //    time in the same k order; 32 consecutive lanes read consecutive floats.
 //  * B rows are the MFMA's M side, so a lane owns one output row and four
 //    consecutive columns per register group.
-// Rates: 92 TFLOP/s at 4096 x 3456 x 1152, 66 at 2048 x 1152 x 1152 (576 tiles on
-// 256 CUs).  Before, the forward ran 64 x 64 tiles of plain FMAs (37 and 25) and
-// the gradients one thread per output (0.7-1.1 TFLOP/s).
+// Rates: 114 TFLOP/s at 4096 x 3456 x 1152 (80% of the matrix cores' rate at the
+// 2.17 GHz the chip runs at), 80 at 2048 x 1152 x 1152 (576 tiles on 256 CUs).
+// Before, the forward ran 64 x 64 tiles of plain FMAs (37 and 25) and the
+// gradients one thread per output (0.7-1.1 TFLOP/s).
 // Any size, stride and 4-byte alignment is accepted: 16-byte loads and stores
 // where the rows allow them, single floats otherwise (a wave-uniform choice).
 #include <math.h>
@@ -54,41 +56,65 @@ struct F32Gemm {
   int64_t lda, ldb, M, N, K;
   uint32_t n_mt, n_nt;
   int epi;
-  bool vec_a, vec_b, vec_n;  // 16-byte accesses allowed for a, b, and all [M][N] arrays
+  bool vec_n;  // 16-byte stores allowed
   RowSwap rs;
 };
 
-// One operand's 32-wide K slice of a ROWS-row tile: global -> registers -> LDS.
-template <int ROWS, bool TRANS>
+// One operand's 32-wide K slices of a 64-row tile: global -> registers -> LDS.
+// VEC: every chunk of 4 floats starts on 16 bytes and lies wholly inside or
+// outside the operand.
+template <bool TRANS, bool VEC>
 struct F32Operand {
-  static constexpr int P = TRANS ? ROWS + 4 : FBK + 4;
-  static constexpr int ELEMS = TRANS ? FBK * P : ROWS * P;
-  static constexpr int LOADS = ROWS * FBK / 4 / FTHR;
-  static constexpr int CPL = TRANS ? ROWS / 4 : FBK / 4;  // chunks per line
+  static constexpr int P = TRANS ? FT + 4 : FBK + 4;
+  static constexpr int ELEMS = TRANS ? FBK * P : FT * P;
+  static constexpr int LOADS = FT * FBK / 4 / FTHR;
+  static constexpr int CPL = TRANS ? FT / 4 : FBK / 4;  // chunks per line
   float4 pre[LOADS];
+  const float* ptr[LOADS];  // each chunk's address in the next slice
+  int rows_in[LOADS];       // rows of the chunk inside the operand (TRANS: 0..4, else 0 or 1)
+  int64_t step;
 
-  // t: thread of the group; [k0, K): the reduction range left
-  __device__ __forceinline__ void load(int t, const float* base, int64_t ld, int64_t r0, int64_t rows, int64_t k0,
-                                       int64_t K, bool vec) {
+  // t: thread of the group; the range starts at reduction index k0.  Chunks of
+  // rows past the end point at the tile's first row: what they load only enters
+  // outputs that are not stored.
+  __device__ __forceinline__ void init(int t, const float* base, int64_t ld, int64_t r0, int64_t rows, int64_t k0) {
+    step = TRANS ? FBK * ld : FBK;
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-      const int e = t + FTHR * i;
-      const int line = e / CPL, c = (e % CPL) * 4;
+      const int line = (t + FTHR * i) / CPL, c = ((t + FTHR * i) % CPL) * 4;
       // element j of the chunk: row r (+ j if TRANS), reduction index k (+ j if not)
       const int64_t r = r0 + (TRANS ? c : line), k = k0 + (TRANS ? line : c);
-      const float* p = base + (TRANS ? k * ld + r : r * ld + k);
-      const bool in = r < rows && k < K;
-      float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      if (vec) {  // rows (TRANS) or the range's end a multiple of 4: the chunk is whole
-        if (in) v = *reinterpret_cast<const float4*>(p);
-      } else if (in) {
-        const int64_t left = TRANS ? rows - r : K - k;
-        v.x = p[0];
-        if (left > 1) v.y = p[1];
-        if (left > 2) v.z = p[2];
-        if (left > 3) v.w = p[3];
+      rows_in[i] = r < rows ? (TRANS ? (int)min(rows - r, (int64_t)4) : 1) : 0;
+      const int64_t rc = r < rows ? r : r0;
+      ptr[i] = base + (TRANS ? k * ld + rc : rc * ld + k);
+    }
+  }
+  // a slice wholly inside the range (VEC only)
+  __device__ __forceinline__ void load_full() {
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      pre[i] = *reinterpret_cast<const float4*>(ptr[i]);
+      ptr[i] += step;
+    }
+  }
+  // any slice: `avail` of its reduction indices are in the range, the rest zero
+  __device__ __forceinline__ void load_masked(int t, int64_t avail) {
+    const int kl = (int)max((int64_t)0, min(avail, (int64_t)FBK));
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      const int line = (t + FTHR * i) / CPL, c = ((t + FTHR * i) % CPL) * 4;
+      const int n = TRANS ? (line < kl ? rows_in[i] : 0) : (rows_in[i] ? kl - c : 0);
+      const float* p = ptr[i];
+      pre[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if constexpr (VEC) {
+        if (n > 0) pre[i] = *reinterpret_cast<const float4*>(p);
+      } else {
+        if (n > 0) pre[i].x = p[0];
+        if (n > 1) pre[i].y = p[1];
+        if (n > 2) pre[i].z = p[2];
+        if (n > 3) pre[i].w = p[3];
       }
-      pre[i] = v;
+      ptr[i] += step;
     }
   }
   __device__ __forceinline__ void store(int t, float* lds) const {
@@ -130,10 +156,10 @@ __device__ __forceinline__ float f32_epilogue(const F32Gemm& p, float v, int64_t
   }
 }
 
-template <bool TA, bool TB, int KS>
+template <bool TA, bool TB, int KS, bool VEC>
 __global__ __launch_bounds__(FTHR* KS) void gemm_f32_mfma_kernel(F32Gemm p) {
-  using OA = F32Operand<FT, TA>;
-  using OB = F32Operand<FT, TB>;
+  using OA = F32Operand<TA, VEC>;
+  using OB = F32Operand<TB, VEC>;
   constexpr int STAGE = OA::ELEMS + OB::ELEMS;
   __shared__ __attribute__((aligned(16))) float lds[KS * 2 * STAGE];
 
@@ -162,34 +188,52 @@ __global__ __launch_bounds__(FTHR* KS) void gemm_f32_mfma_kernel(F32Gemm p) {
   const int64_t slices = (p.K + FBK - 1) / FBK, steps = (slices + KS - 1) / KS;
   const int64_t kb = ks * steps * FBK, ke = min(p.K, kb + steps * FBK);
   float* stage = lds + ks * 2 * STAGE;
-  oa.load(t, p.a, p.lda, m0, p.M, kb, ke, p.vec_a);
-  ob.load(t, p.b, p.ldb, n0, p.N, kb, ke, p.vec_b);
+  oa.init(t, p.a, p.lda, m0, p.M, kb);
+  ob.init(t, p.b, p.ldb, n0, p.N, kb);
+  oa.load_masked(t, ke - kb);
+  ob.load_masked(t, ke - kb);
   oa.store(t, stage);
   ob.store(t, stage + OA::ELEMS);
   __syncthreads();
-  int buf = 0;
-  for (int64_t st = 0; st < steps; ++st, buf ^= 1) {
-    const bool more = st + 1 < steps;
-    if (more) {
-      oa.load(t, p.a, p.lda, m0, p.M, kb + (st + 1) * FBK, ke, p.vec_a);
-      ob.load(t, p.b, p.ldb, n0, p.N, kb + (st + 1) * FBK, ke, p.vec_b);
-    }
+  // one slice; `next` issues the next one's loads behind the first fragment reads
+  auto slice = [&](int buf, auto next) {
     const float* As = stage + buf * STAGE;
     const float* Bs = As + OA::ELEMS;
 #pragma unroll
     for (int c8 = 0; c8 < FBK / 8; ++c8) {
       const float4 af = OA::frag(As, wm + l32, c8, g), bf = OB::frag(Bs, wn + l32, c8, g);
+      if (c8 == 0) next();
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf.x, af.x, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf.y, af.y, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf.z, af.z, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf.w, af.w, acc, 0, 0, 0);
     }
-    if (more) {  // the other buffer was last read before the previous barrier
-      oa.store(t, stage + (buf ^ 1) * STAGE);
-      ob.store(t, stage + (buf ^ 1) * STAGE + OA::ELEMS);
-      __syncthreads();
-    }
+  };
+  auto put = [&](int buf) {  // this buffer was last read before the previous barrier
+    oa.store(t, stage + buf * STAGE);
+    ob.store(t, stage + buf * STAGE + OA::ELEMS);
+    __syncthreads();
+  };
+  // Slices that are whole in every group load without a mask or a branch (a
+  // branch between two ways to load made every slice wait for its own loads:
+  // 352 against 309 us at 4096 x 3456 x 1152); the rest of the range follows.
+  const int64_t whole = VEC ? min(steps, max((int64_t)0, (p.K - (KS - 1) * steps * FBK) / FBK)) : 0;
+  int64_t st = 0;
+  for (; st + 1 < whole; ++st) {
+    slice(st & 1, [&] {
+      oa.load_full();
+      ob.load_full();
+    });
+    put((st + 1) & 1);
   }
+  for (; st + 1 < steps; ++st) {
+    slice(st & 1, [&] {
+      oa.load_masked(t, ke - kb - (st + 1) * FBK);
+      ob.load_masked(t, ke - kb - (st + 1) * FBK);
+    });
+    put((st + 1) & 1);
+  }
+  slice(st & 1, [] {});
   if constexpr (KS > 1) {
     // groups 1 .. KS - 1 leave their sums in LDS, group 0 adds them in order
     static_assert((KS - 1) * FTHR * 16 <= KS * 2 * STAGE, "the partial sums fit the buffers");
@@ -234,14 +278,15 @@ bool al16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 // Groups per tile: as many as keep the whole grid resident at once (256 CUs, at
 // most 16 waves on each), while each still has a few slices.  us with 1 / 2 / 4
-// groups, K = 1152: 72 tiles 42.5 / 34 / 31, 288 tiles 61 / 55 / 62, 576 tiles
-// 82 / 106 / 94; K = 4608: 72 tiles 238 / 162 / 121, 288 tiles 238 / 205 / 240.
+// groups (masked loads), K = 1152: 72 tiles 42.5 / 34 / 31, 288 tiles 61 / 55 / 62,
+// 576 tiles 82 / 106 / 94; K = 4608: 72 tiles 238 / 162 / 121, 288 tiles 238 / 205 /
+// 240.  With whole slices loaded unmasked: 26 and 49 us (K = 1152, 72 and 288 tiles).
 
 template <bool TA, bool TB>
 int launch_f32(F32Gemm p, hipStream_t s) {
   if (p.M == 0 || p.N == 0) return DSP_OK;
-  p.vec_a = al16(p.a) && p.lda % 4 == 0 && (TA ? p.M : p.K) % 4 == 0;
-  p.vec_b = al16(p.b) && p.ldb % 4 == 0 && (TB ? p.N : p.K) % 4 == 0;
+  const bool vec = al16(p.a) && p.lda % 4 == 0 && (TA ? p.M : p.K) % 4 == 0 && al16(p.b) && p.ldb % 4 == 0 &&
+                   (TB ? p.N : p.K) % 4 == 0;
   p.vec_n = al16(p.out) && p.N % 4 == 0;
   const int64_t n_mt = (p.M + FT - 1) / FT, n_nt = (p.N + FT - 1) / FT;
   // (tile indices and the 8-tile group size are 32-bit)
@@ -252,12 +297,21 @@ int launch_f32(F32Gemm p, hipStream_t s) {
   const int64_t tiles = n_mt * n_nt;
   const dim3 grid((uint32_t)tiles);
   const int ks = tiles <= 256 && p.K >= 16 * FBK ? 4 : tiles <= 512 && p.K >= 8 * FBK ? 2 : 1;
+  const dim3 block((uint32_t)(ks * FTHR));
+#define DSP_F32_LAUNCH(KS_)                                                               \
+  do {                                                                                    \
+    if (vec)                                                                              \
+      hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, KS_, true>), grid, block, 0, s, p);  \
+    else                                                                                  \
+      hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, KS_, false>), grid, block, 0, s, p); \
+  } while (0)
   if (ks == 4)
-    hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, 4>), grid, dim3(4 * FTHR), 0, s, p);
+    DSP_F32_LAUNCH(4);
   else if (ks == 2)
-    hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, 2>), grid, dim3(2 * FTHR), 0, s, p);
+    DSP_F32_LAUNCH(2);
   else
-    hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, 1>), grid, dim3(FTHR), 0, s, p);
+    DSP_F32_LAUNCH(1);
+#undef DSP_F32_LAUNCH
   return last_launch_status();
 }
 
