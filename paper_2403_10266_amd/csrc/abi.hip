@@ -371,15 +371,15 @@ bool block_ws_layout(int64_t B, int64_t T, int64_t S, int C, int F, int dtype, B
 // (switched to (B, S, T, C)) and r2 that the first two LayerNorms normalise,
 // and r3, the sum the MLP's LayerNorm normalises, gets a slot of its own.
 // u is what the MLP activation's backward needs: the pre-activation, or with
-// GELU in bf16 at sizes whose backward runs on the large-tile GEMM, GELU' at
+// GELU in bf16 at sizes whose backward runs on the forward's tiles, GELU' at
 // the fp32 pre-activation (block_keeps_act_grad), so that the backward's
 // epilogue is one multiply instead of the derivative's evaluation.
 struct BlockSaved {
   size_t y0, y1, h1, qkv1, a1, lse1, h2, qkv2, a2, lse2, h3, u, g, r3, total;
 };
 
-bool block_keeps_act_grad(int64_t tokens, int F, int dtype, int flags) {
-  return dtype == DSP_BF16 && !(flags & DSP_BLOCK_RELU) && linear_bf16_large_tiles(tokens, F);
+bool block_keeps_act_grad(int64_t tokens, int C, int F, int dtype, int flags) {
+  return dtype == DSP_BF16 && !(flags & DSP_BLOCK_RELU) && linear_bf16_tiled(tokens, F, C);
 }
 
 bool block_saved_layout(int64_t B, int64_t T, int64_t S, int C, int H, int F, int flags, int dtype,
@@ -1007,7 +1007,7 @@ int dsp_st_block_forward_train(const float* x_BTSC, float* y_BSTC, const dsp_blo
   const int D = C / H;
   const int act = (flags & DSP_BLOCK_RELU) ? DSP_EPI_RELU : DSP_EPI_GELU;
   // what the MLP's first GEMM keeps in `u` (see block_keeps_act_grad)
-  const int act_keep = block_keeps_act_grad(tokens, F, dtype, flags) ? DSP_EPI_GELU_KEEP_GRAD : act;
+  const int act_keep = block_keeps_act_grad(tokens, C, F, dtype, flags) ? DSP_EPI_GELU_KEEP_GRAD : act;
   RowSwap swap;  // (B, T, S) token rows -> (B, S, T)
   swap.outer = (uint32_t)T;
   swap.inner = (uint32_t)S;
@@ -1121,7 +1121,7 @@ int dsp_st_block_backward(const float* x_BTSC, const float* dy_BSTC, const dsp_b
   const int D = C / H;
   const int act_epi = bf ? DSP_GRAD_EPI_BF16 : DSP_GRAD_EPI_F32;   // gradients fed to bf16 / fp32 operands
   const int act_bwd = (flags & DSP_BLOCK_RELU) ? DSP_GRAD_EPI_RELU_BWD : DSP_GRAD_EPI_GELU_BWD;
-  const bool kept_grad = block_keeps_act_grad(tokens, F, dtype, flags);
+  const bool kept_grad = block_keeps_act_grad(tokens, C, F, dtype, flags);
   RowSwap back;  // (B, S, T) token rows -> (B, T, S): the Switch's adjoint
   back.outer = (uint32_t)S;
   back.inner = (uint32_t)T;
@@ -1133,9 +1133,9 @@ int dsp_st_block_backward(const float* x_BTSC, const float* dy_BSTC, const dsp_b
   // the upstream fp32 gradient as an operand of the block dtype
   auto operand = [&](const float* d) { return launch_cast(d, 0, dyb, bf, tokens * C, s); };
   // dx = dy W (+ the activation's derivative) for W stored [N][K]: in bf16 at
-  // sizes the forward's large-tile GEMM takes, dx = dy (W^T)^T runs on that
+  // sizes the forward's pipelined or large tiles take, dx = dy (W^T)^T runs on that
   // GEMM with W^T from the workspace; else the gradient GEMM.  The weights
-  // taking the large tiles are transposed first, all in one launch.
+  // it takes are transposed first, all in one launch.
   struct Transposed {
     const void* w;
     int N, K;
@@ -1151,7 +1151,7 @@ int dsp_st_block_backward(const float* x_BTSC, const float* dy_BSTC, const dsp_b
     int64_t rows[6], cols[6];
     size_t off = 0;
     for (int i = 0; i < 6; ++i) {
-      if (!linear_bf16_large_tiles(tokens, nk[i][1])) continue;
+      if (!linear_bf16_tiled(tokens, nk[i][1], nk[i][0])) continue;
       void* dst = static_cast<char*>(wt) + off;
       off += ((size_t)nk[i][0] * nk[i][1] * es + 255) & ~size_t(255);
       tw[n_tw] = {src[i], nk[i][0], nk[i][1], dst};
@@ -1164,11 +1164,11 @@ int dsp_st_block_backward(const float* x_BTSC, const float* dy_BSTC, const dsp_b
     if (n_tw) DSP_TRY(launch_transpose_bf16_batch(xs, ys, rows, cols, n_tw, s));
   }
   auto bwd_data = [&](const void* dyp, const void* wp, const void* up, void* dxp, int N, int K, int epi) -> int {
-    if (bf && linear_bf16_large_tiles(tokens, K)) {
+    if (bf && linear_bf16_tiled(tokens, K, N)) {
       const void* wtp = nullptr;
       for (int i = 0; i < n_tw; ++i)
         if (tw[i].w == wp && tw[i].N == N && tw[i].K == K) wtp = tw[i].wt;
-      if (!wtp) return DSP_ERR_ARG;  // every large-tile weight was transposed above
+      if (!wtp) return DSP_ERR_ARG;  // every such weight was transposed above
       const int e = epi == DSP_GRAD_EPI_F32 ? DSP_EPI_F32
                     : epi == DSP_GRAD_EPI_BF16 ? DSP_EPI_NONE
                     : epi == DSP_GRAD_EPI_GELU_BWD ? (kept_grad ? DSP_EPI_SCALE_BWD : DSP_EPI_GELU_BWD)

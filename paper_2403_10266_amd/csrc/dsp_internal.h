@@ -147,8 +147,9 @@ constexpr int DSP_EPI_GELU_BWD = 5, DSP_EPI_RELU_BWD = 6;
 // out = (a W^T) * f with f read from `pre`.  Together they turn the
 // activation's backward epilogue into one multiply.
 constexpr int DSP_EPI_GELU_KEEP_GRAD = 7, DSP_EPI_SCALE_BWD = 8;
-// Whether launch_linear_bf16 runs (M, N) on its large-tile kernel.
-bool linear_bf16_large_tiles(int64_t M, int N);
+// Whether launch_linear_bf16 runs (M, N, K) on its pipelined or large tiles (not
+// on the 256 x 128 kernel it keeps for the other sizes).
+bool linear_bf16_tiled(int64_t M, int64_t N, int64_t K);
 // y_i[c][r] = x_i[r][c] for n <= 6 bf16 matrices of rows_i x cols_i (multiples
 // of 8, 16-byte aligned), in one launch (gemm.hip).
 int launch_transpose_bf16_batch(const void* const* x, void* const* y, const int64_t* rows, const int64_t* cols,

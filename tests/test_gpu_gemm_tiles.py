@@ -1,0 +1,65 @@
+"""The bf16 GEMM's pipelined tiles against float64: every tile shape (64 x 64, 64 x 128,
+128 x 128 with two and four K slices in flight, 128 x 192), fewer K slices than
+buffers, partial tiles on both sides, and each epilogue.
+
+Bound per output: fp32 accumulation of K bf16 products is off by at most
+(K + 4) 2^-24 sum |a| |w| (bias and residual included in the sum), the GELU
+evaluation by 1e-6 of that magnitude, and a bf16 result by its rounding: half an ulp
+of 8 significant bits, 2^-8 of the value."""
+import pytest
+
+import synth
+from tests.gpu_util import say
+from tests.test_gpu_block_bwd import _train_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    return torch
+
+
+@pytest.mark.parametrize("epi", ["none", "gelu", "relu", "resid", "f32"])
+@pytest.mark.parametrize("M,N,K", [
+    (1, 8, 64), (63, 72, 128), (65, 200, 192), (100, 64, 256), (130, 1160, 320),   # 64 x 64: 1 to 5 slices, 4 buffers
+    (1201, 4600, 1152),     # 64 x 128
+    (2500, 1152, 192),      # 128 x 128, four slices in flight, three slices
+    (4501, 3464, 1152),     # 128 x 128, two work-groups per CU
+    (8001, 1160, 1152),     # 128 x 192
+])
+def test_gemm_tiles(torch, M, N, K, epi):
+    import paper_2403_10266_amd as dsp
+    gen = torch.Generator(device="cuda:0").manual_seed(M + N + K)
+
+    def draw(*s):
+        return torch.randn(s, generator=gen, device="cuda:0")
+
+    a, w, b = (draw(*s).to(torch.bfloat16) for s in ((M, K), (N, K), (N,)))
+    r = draw(M, N) if epi == "resid" else None
+    code = {"none": dsp.DSP_EPI_NONE, "gelu": dsp.DSP_EPI_GELU, "relu": dsp.DSP_EPI_RELU, "resid": dsp.DSP_EPI_RESID,
+            "f32": dsp.DSP_EPI_F32}[epi]
+    say(f"gemm tiles M={M} N={N} K={K} {epi}")
+    got = dsp.dsp_linear(a, w, b, r, code).double()
+    want = a.double() @ w.double().t() + b.double()
+    mag = a.double().abs() @ w.double().abs().t() + b.double().abs()
+    if epi == "resid":
+        want, mag = want + r.double(), mag + r.double().abs()
+    bound = (K + 4) * 2.0 ** -24 * mag
+    if epi == "gelu":
+        want, bound = torch.nn.functional.gelu(want), 1.2 * bound + 1e-6 * (1 + want.abs())   # |GELU'| < 1.13
+    elif epi == "relu":
+        want = torch.relu(want)
+    if epi not in ("resid", "f32"):
+        bound = bound + 2.0 ** -8 * (want.abs() + bound)
+    err = (got - want).abs()
+    assert bool((err <= bound).all()), float((err - bound).max())
+
+
+@pytest.mark.parametrize("flags,T,S", [(0, 3, 10), (4, 5, 40)])
+def test_block_train_small_tiles(torch, flags, T, S):
+    """Few tokens at widths that are multiples of 64: the training epilogues (kept
+    derivative, its use in the backward) on 64-row tiles."""
+    w = synth.Workload("block_64", "block", "bf16", B=2, T=T, S=S, C=128, H=2, F=256, seed=31)
+    _train_case(torch, w, True, flags)
