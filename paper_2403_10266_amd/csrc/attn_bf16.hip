@@ -767,11 +767,59 @@ int launch_cfg(const AttnArgs& a, hipStream_t s) {
   return last_launch_status();
 }
 
+// Queries per work-group for more than 128 keys.  512 (8 waves of 64, one
+// work-group per CU) reads K and V least often, but few or ragged units then
+// leave CUs idle in the last round of work-groups: 7 frames of 1350 tokens and
+// 16 heads are 336 work-groups, two rounds for 1.3.  256 (4 waves of 64) and 128
+// (4 waves of 32, which read every K and V fragment for half the work) put two and
+// three work-groups on a CU.  Times in microseconds, t = 64-key tiles: 512 queries
+// take 6.2 + 1.93 t for one round of 256 work-groups and 7.1 + 2.09 t for each of
+// several; the smaller blocks, whose rounds overlap, 3.9 + full rounds of 256 *
+// levels work-groups and one of the rest, with 1 .. levels of them per CU, a round with
+// j per CU taking a[j - 1] + b[j - 1] t.  Fitted to 87 measured shapes (D = 72 and 64, 150
+// to 4096 queries, 150 to 4096 keys, 16 to 800 units; relative error 4-8%); choosing by it
+// costs 0.9% on average against each shape's best of the three and takes 23% off what
+// 512 queries need: 7 x 1350 (16 heads) 96 -> 80 us, 60 x 250 57 -> 37, 34 x 400 62 -> 50;
+// 32 x 1024 and 32 x 4096 stay on 512 (180 against 183, 2330 against 2410 us with 256).
+struct QueryBlock {
+  int queries, levels;
+  double a[3], b[3];
+};
+constexpr int kMaxQueryBlock = 512;
+constexpr QueryBlock kSmallBlocks[2] = {{256, 2, {1.4, 4.8}, {1.38, 2.20}},
+                                        {128, 3, {0.4, 2.2, 3.8}, {0.90, 1.35, 1.84}}};
+
+int choose_queries(int64_t units, int64_t L, int64_t Lk) {
+  const double tiles = (double)((Lk + 63) / 64);
+  const int64_t rounds = (units * ((L + kMaxQueryBlock - 1) / kMaxQueryBlock) + 255) / 256;
+  int best = kMaxQueryBlock;
+  double best_cost = rounds == 1 ? 6.2 + 1.93 * tiles : (double)rounds * (7.1 + 2.09 * tiles);
+  for (const QueryBlock& q : kSmallBlocks) {
+    const int64_t blocks = units * ((L + q.queries - 1) / q.queries), round = 256 * q.levels, rest = blocks % round;
+    double cost = 3.9 + (double)(blocks / round) * (q.a[q.levels - 1] + q.b[q.levels - 1] * tiles);
+    if (rest) {
+      const int j = (int)((rest + 255) / 256) - 1;
+      cost += q.a[j] + q.b[j] * tiles;
+    }
+    if (cost < best_cost) {
+      best = q.queries;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 template <int D>
 int launch_d(const AttnArgs& a, hipStream_t s) {
   // few keys: all of a unit's keys are one tile, fetched at once (the tiling
-  // is chosen by the key count; any number of queries runs in query blocks)
-  if (a.Lk <= 32) return launch_cfg<D, 1, 1, 32, 1, 1>(a, s);
+  // is chosen by the key count; any number of queries runs in query blocks).
+  // At most 32 keys: one wave and a 32-key tile suit few queries (150: 13.0
+  // against 15.0 us for 800 units), four waves on a half-empty 64-key tile many
+  // (1024: 45 -> 33 us, 300: 5.4 -> 5.1 for 32 units).
+  if (a.Lk <= 32) {
+    if (a.L >= 256) return launch_cfg<D, 4, 1, 64, 3, 1>(a, s);
+    return launch_cfg<D, 1, 1, 32, 1, 1>(a, s);
+  }
   if (a.Lk <= 64) return launch_cfg<D, 2, 1, 64, 2, 1>(a, s);
   if (a.Lk <= 128) {
     if constexpr (DSP_TATTN_KB >= 128)
@@ -779,7 +827,12 @@ int launch_d(const AttnArgs& a, hipStream_t s) {
     else
       return launch_cfg<D, DSP_TATTN_NW, DSP_TATTN_QT, DSP_TATTN_KB, DSP_TATTN_MINW>(a, s);
   }
-  return launch_cfg<D, DSP_SATTN_NW, DSP_SATTN_QT, DSP_SATTN_KB, DSP_SATTN_MINW>(a, s);
+  static_assert(DSP_SATTN_NW * DSP_SATTN_QT * 32 == kMaxQueryBlock, "the largest query block");
+  switch (choose_queries(a.B * a.X * a.H, a.L, a.Lk)) {
+    case 256: return launch_cfg<D, 4, 2, 64, 2>(a, s);
+    case 128: return launch_cfg<D, 4, 1, 64, 3>(a, s);
+    default: return launch_cfg<D, DSP_SATTN_NW, DSP_SATTN_QT, DSP_SATTN_KB, DSP_SATTN_MINW>(a, s);
+  }
 }
 
 }  // namespace
