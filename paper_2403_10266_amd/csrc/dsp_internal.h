@@ -96,8 +96,9 @@ int launch_layernorm(const void* x, int x_bf16, void* y, int y_bf16, int64_t row
 
 // Gradient GEMMs (gemm_grad.hip): out[m][n] = sum_k A(m, k) B(n, k) with
 // A(m, k) = a[m * lda + k] (ta = 0) or a[k * lda + m] (ta = 1), B likewise.
-// epi: DSP_GRAD_EPI_*.  splits > 1 (fp32 output only) uses ws, fp32
-// [splits][M][N].  bf16 needs M, N, K multiples of 8 (checked by the ABI).
+// epi: DSP_GRAD_EPI_*.  Layouts: (ta, tb) = (0, 1), dx, and (1, 1), dW (fp32 output),
+// which cuts the reduction into at most `splits` partials in ws, fp32
+// [splits][M][N].  bf16 needs M, N (and dx's K) multiples of 8 (checked by the ABI).
 int grad_splits(int64_t M, int64_t N, int64_t K);
 bool grad_gemm_fits(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb);
 int launch_gemm_grad(const void* a, int ta, int64_t lda, const void* b, int tb, int64_t ldb, const void* aux,

@@ -24,6 +24,7 @@
 
 #include <type_traits>
 
+#include "direct_lds.h"
 #include "dsp_internal.h"
 
 // Large-tile kernel for problems of at least one full round of 256 x 192/256 tiles.
@@ -38,7 +39,6 @@ typedef __bf16 bf16;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BM = 256, BN = 128, BK = 64;
@@ -687,39 +687,6 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_bf16_big_kernel(
       }
     }
   }
-}
-
-// ---- direct global-to-LDS loads, issued and waited for by hand.
-// The compiler cannot tell which LDS reads depend on which of these loads and
-// would wait for all of them before every read; written as assembly (they
-// have no output register) they stay in flight across several K slices, and
-// wait_barrier() states how many may.  Loads return in order, and the
-// compiler's own waits count only its own loads, so they wait longer, never
-// shorter, than they need.
-__device__ __forceinline__ u32x4 dma_rsrc(const void* base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  u32x4 r;
-  r[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  r[2] = __builtin_amdgcn_readfirstlane(bytes);
-  r[3] = 0x00020000u;
-  return r;
-}
-// 16 bytes per lane from rsrc + voff + soff to LDS address `at` + 16 lane
-// (`at`, soff: wave-uniform).  m0 holds `at`; nothing else in these kernels uses
-// it (it is a reserved register, which a clobber list may not name).
-__device__ __forceinline__ void dma_b128(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t at) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(at), "v"(voff), "s"(rsrc), "s"(soff)
-               : "memory");
-}
-// at most N of this wave's loads in flight, all its LDS reads returned, then
-// the work-group's barrier
-template <int N>
-__device__ __forceinline__ void wait_barrier() {
-  static_assert(N < 64, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
 }
 
 // Tiles of 64 TM x 64 TN (4 waves of 32 TM x 32 TN), K a multiple of 64: slices of

@@ -3,35 +3,32 @@
 // as in the forward), the gradients are
 //   dx = dy W          -- [tokens, in]  = [tokens, out] x [out, in]
 //   dW = dy^T x        -- [out, in]     = [out, tokens] x [tokens, in]
-// so one operand, or both, has its reduction index strided in memory.  This
-// kernel computes out[m][n] = sum_k A(m, k) B(n, k) for either storage of each
-// operand:  A(m, k) = a[m * lda + k] (TA = 0) or a[k * lda + m] (TA = 1), and
-// the same for B with TB.
+// so one operand, or both, has its reduction index strided in memory.  (The block's
+// bf16 backward transposes its weights once and takes dx through the forward's
+// tiles where it can; the dx kernel here serves dsp_linear_bwd_data and widths that
+// are not multiples of 64.)
 //
-// Design for gfx950, on v_mfma_f32_32x32x16_bf16 like the forward GEMM
-// (256 x 128 tiles, 4 waves of 128 x 64, 64-wide k slices through LDS, the next
-// slice prefetched into registers, B rows on the MFMA M side so a lane owns one
-// output row):
-//  * An operand stored with the reduction contiguous keeps the forward's LDS
-//    layout [rows][k] (144-byte rows).  One stored transposed is copied as it
-//    lies, [k][rows] (rows contiguous, 16-byte chunks), and its MFMA fragments
-//    are read with ds_read_b64_tr_b16, which gives each lane 8 k values of one
-//    row in the order {4g..4g+3, 8+4g..8+4g+3} of a 16-k step.  The natural
-//    operand is read in the same k order (two 8-byte reads), so the two sides
-//    of every MFMA agree.
-//  * Split-K: the reduction range is cut into `splits` parts, one per grid z;
-//    each writes fp32 partial sums to its own slab of a workspace and a second
-//    kernel adds the slabs in a fixed order (no atomics: deterministic).  The
-//    weight gradients reduce over all tokens (32768 at the block's size) onto
-//    few output tiles, which is what this is for.
-//  * Epilogues: fp32 output; bf16 output; the GELU / ReLU backward, out =
+// Design for gfx950, on v_mfma_f32_32x32x16_bf16 like the forward GEMM, B rows on the
+// MFMA M side so a lane owns one output row:
+//  * dx: 256 x 128 tiles, 4 waves of 128 x 64, 64-wide k slices through LDS, the next
+//    slice prefetched into registers.  dy keeps the forward's LDS layout [rows][k]
+//    (144-byte rows); W is copied as it lies, [k][rows], and its fragments are
+//    read with ds_read_b64_tr_b16, which gives each lane 8 k values of one row in
+//    the order {4g..4g+3, 8+4g..8+4g+3} of a 16-k step.  dy is then read in the same
+//    k order (two 8-byte reads), so the two sides of every MFMA agree.
+//    Epilogues: fp32 output; bf16 output; the GELU / ReLU backward, out =
 //    acc * act'(u) with u the saved pre-activation (bf16), rounded to bf16.
+//  * dW: gemm_grad_tt_dma_kernel below.  The reduction over all tokens is cut into
+//    splits, one per grid z; each writes fp32 partial sums to its own slab of a
+//    workspace and a second kernel adds the slabs in a fixed order (no atomics:
+//    deterministic).
 #include <math.h>
 
 #include <algorithm>
 #include <type_traits>
 
 #include "attn_bf16_common.h"
+#include "direct_lds.h"
 #include "dsp_internal.h"
 
 namespace dsp {
@@ -159,10 +156,10 @@ struct Operand {
   }
 };
 
-template <bool TA, bool TB, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(GNTHR, 2) void gemm_grad_kernel(GradArgs p) {
-  using OA = Operand<GBM, TA>;
-  using OB = Operand<GBN, TB>;
+  using OA = Operand<GBM, false>;
+  using OB = Operand<GBN, true>;
   __shared__ __attribute__((aligned(16))) bf16 As[OA::ELEMS];
   __shared__ __attribute__((aligned(16))) bf16 Bs[OB::ELEMS];
 
@@ -172,8 +169,6 @@ __global__ __launch_bounds__(GNTHR, 2) void gemm_grad_kernel(GradArgs p) {
   const int mt = bid / p.n_ntiles;
   const int nt = bid - mt * p.n_ntiles;
   const int m0 = mt * GBM, n0 = nt * GBN;
-  const int kb = blockIdx.z * p.k_per_split;
-  const int ke = min(p.K, kb + p.k_per_split);
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -182,8 +177,8 @@ __global__ __launch_bounds__(GNTHR, 2) void gemm_grad_kernel(GradArgs p) {
 
   OA a;
   OB b;
-  a.init(p.a, p.lda, m0, p.M, ke);
-  b.init(p.b, p.ldb, n0, p.N, ke);
+  a.init(p.a, p.lda, m0, p.M, p.K);
+  b.init(p.b, p.ldb, n0, p.N, p.K);
 
   floatx16 acc[2][4];
 #pragma unroll
@@ -193,10 +188,10 @@ __global__ __launch_bounds__(GNTHR, 2) void gemm_grad_kernel(GradArgs p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  const int nk = (ke - kb + GBK - 1) / GBK;
+  const int nk = (p.K + GBK - 1) / GBK;
   if (nk > 0) {
-    a.load(kb);
-    b.load(kb);
+    a.load(0);
+    b.load(0);
     a.store(As);
     b.store(Bs);
   }
@@ -204,8 +199,8 @@ __global__ __launch_bounds__(GNTHR, 2) void gemm_grad_kernel(GradArgs p) {
   for (int it = 0; it < nk; ++it) {
     const bool more = it + 1 < nk;
     if (more) {
-      a.load(kb + (it + 1) * GBK);
-      b.load(kb + (it + 1) * GBK);
+      a.load((it + 1) * GBK);
+      b.load((it + 1) * GBK);
     }
 #pragma unroll
     for (int ks = 0; ks < GBK / 16; ++ks) {
@@ -229,7 +224,6 @@ __global__ __launch_bounds__(GNTHR, 2) void gemm_grad_kernel(GradArgs p) {
   }
 
   // epilogue: lane owns row m = .. + l32 and columns n = .. + 8 r4 + 4g + {0..3}
-  const int64_t slab = (int64_t)blockIdx.z * p.M * p.N;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int m = m0 + wm * 128 + 32 * j + l32;
@@ -245,7 +239,7 @@ __global__ __launch_bounds__(GNTHR, 2) void gemm_grad_kernel(GradArgs p) {
         for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * r4 + e];
         const int64_t off = (int64_t)m * p.N + n;
         if (EPI == DSP_GRAD_EPI_F32) {
-          *reinterpret_cast<float4*>(static_cast<float*>(p.out) + slab + off) = make_float4(v[0], v[1], v[2], v[3]);
+          *reinterpret_cast<float4*>(static_cast<float*>(p.out) + off) = make_float4(v[0], v[1], v[2], v[3]);
         } else {
           if (EPI == DSP_GRAD_EPI_GELU_BWD || EPI == DSP_GRAD_EPI_RELU_BWD) {
             const uint2 uw = *reinterpret_cast<const uint2*>(p.aux + off);
@@ -346,42 +340,47 @@ __global__ __launch_bounds__(CS_THREADS) void colsum_kernel(const void* __restri
 }
 
 // ---------------------------------------------------------------------------
-// Large-tile weight gradient: out[M][N] = sum over k of a[k][m] b[k][n] (both
-// operands stored with the reduction index as rows: dW = dy^T x), fp32, with
-// the reduction split over blockIdx.z into fp32 partials.  The schedule of
-// gemm_bf16_big_kernel (gemm.hip): 256 x (64 TN) output tiles, 4 waves of
-// 128 x (32 TN) on one SIMD each with the accumulators in AGPRs, two LDS
-// buffers and one barrier per 64-wide k slice (before its last 16-wide step),
-// the next slice's LDS stores and the loads after them spread over the MFMAs
-// of steps 0-2, each step's fragments read during the previous step's MFMAs.  Tiles
-// hold k rows of the tile's columns as they lie in memory; fragments are read
-// with ds_read_b64_tr_b16 (k order {4g..4g+3, 8+4g..8+4g+3} on both sides).
-constexpr int GB_BM = 256;
-#ifndef DSP_GRAD_BIG
-#define DSP_GRAD_BIG 1
-#endif
+// Weight gradient: out[M][N] = sum over k of a[k][m] b[k][n] (both operands stored
+// with the reduction index as rows: dW = dy^T x), fp32, the reduction split over
+// blockIdx.z into fp32 partials.  Tiles of 64 TM x 64 TN (4 waves of 32 TM x 32 TN): the
+// k rows of both operands go from memory straight into a ring of NS LDS buffers of 64
+// rows, and OCC work-groups share a CU (see gemm_bf16_dma_kernel in gemm.hip, whose
+// schedule this is).  Fragments are read with ds_read_b64_tr_b16 (k order
+// {4g..4g+3, 8+4g..8+4g+3} on both sides).  Rows lie unpadded; the 16-byte chunk p of
+// row r holds columns of logical chunk p ^ f(r), where f spreads the four consecutive
+// rows of a transposed read over the banks: 64-byte groups are exchanged by the row's
+// two low bits where a row is a multiple of 256 bytes, by its second bit where it is
+// 128 off one.  Columns past the end re-read the last whole chunk (they only enter
+// outputs that are not stored); a slice that ends before 64 rows is loaded through
+// registers, zero-filled, after the whole ones.
+//   Bound by LDS bandwidth, as the forward's tiles.  13600 tokens, us: 3456 x 1152
+// 135 -> 114, 4608 x 1152 181 -> 151, 1152 x 4608 204 -> 152, 1152 x 1152 70 -> 53 (with the
+// partials' reduction; before: register-staged 256-wide tiles, one work-group per CU);
+// 2000 tokens, 1152 x 1152: 50 -> 17 (256 x 128 tiles before).
+template <int TM, int TN, int NS, int OCC>
+__global__ __launch_bounds__(GNTHR, OCC) void gemm_grad_tt_dma_kernel(GradArgs p) {
+  constexpr int BMT = 64 * TM, BNT = 64 * TN;
+  constexpr int CA = BMT / 8, CB = BNT / 8;   // 16-byte chunks per k row
+  constexpr int STAGE = GBK * (BMT + BNT);    // elements of one slice of both operands
+  constexpr int NP = TM >= 2 ? 2 : 1, RPP = BMT / NP, HR = RPP / 2, BPP = TM / NP;
+  constexpr int SPF = BNT + 4;                // staged output row pitch (fp32)
+  constexpr int LDS_ELEMS = NS * STAGE > RPP * SPF * 2 ? NS * STAGE : RPP * SPF * 2;
+  __shared__ __attribute__((aligned(1024))) bf16 lds[LDS_ELEMS];
 
-template <int TN>
-__global__ __launch_bounds__(GNTHR, 1) void gemm_grad_tt_big_kernel(GradArgs p) {
-  constexpr int TM = 4;
-  constexpr int BNB = 2 * TN * 32;
-  constexpr int PA = GB_BM + 8, PB = BNB + 8;   // k-row pitches: odd multiples of 16 bytes
-  constexpr int A_EL = GBK * PA, STAGE = A_EL + GBK * PB;
-  constexpr int CA = GB_BM / 8, CB = BNB / 8;   // 16-byte chunks per k row
-  constexpr int A_LOADS = GBK * CA / GNTHR, B_LOADS = GBK * CB / GNTHR, NL = A_LOADS + B_LOADS;
-  static_assert(GBK * CA % GNTHR == 0 && GBK * CB % GNTHR == 0, "loader shape");
-  __shared__ __attribute__((aligned(16))) bf16 lds[2 * STAGE];
-
-  // tile order: contiguous ranges per XCD, then groups of 4 m-tiles (m fastest)
+  // tile order: contiguous ranges per XCD, m fastest within groups of 1024 rows
   uint32_t bid = blockIdx.x;
-  if ((p.n_tiles & 7) == 0) bid = (bid & 7u) * ((uint32_t)p.n_tiles >> 3) + (bid >> 3);
+  {
+    const uint32_t per = (uint32_t)p.n_tiles >> 3, extra = (uint32_t)p.n_tiles & 7u, xcd = bid & 7u;
+    bid = xcd * per + min(xcd, extra) + (bid >> 3);
+  }
+  constexpr int GROUP = 1024 / BMT;
   const int n_mt = p.n_tiles / p.n_ntiles;
-  const int per_group = 4 * p.n_ntiles;
+  const int per_group = GROUP * p.n_ntiles;
   const int grp = (int)bid / per_group;
-  const int first_m = grp * 4;
-  const int gm = min(4, n_mt - first_m);
+  const int first_m = grp * GROUP;
+  const int gm = min(GROUP, n_mt - first_m);
   const int rem = (int)bid - grp * per_group;
-  const int m0 = (first_m + rem % gm) * GB_BM, n0 = (rem / gm) * BNB;
+  const int m0 = (first_m + rem % gm) * BMT, n0 = (rem / gm) * BNT;
   const int kb = blockIdx.z * p.k_per_split;
   const int ke = min(p.K, kb + p.k_per_split);
 
@@ -391,32 +390,31 @@ __global__ __launch_bounds__(GNTHR, 1) void gemm_grad_tt_big_kernel(GradArgs p) 
   const int l32 = lane & 31, g = lane >> 5;
   const int j16 = lane & 15, mbase = 16 * ((lane >> 4) & 1);
 
-  // loader: chunk e = t + 256 i of a tensor's slice is k row e / C, columns
-  // 8 (e % C) .. + 7 of the tile; columns past M (N) read zero
-  uint32_t off[NL];
-  int lofs[NL];
-  bool ok[NL];
+  constexpr int A_LOADS = GBK * CA / GNTHR, B_LOADS = GBK * CB / GNTHR, NL = A_LOADS + B_LOADS;
+  auto swz = [](int chunks, int row) { return chunks % 16 == 0 ? (row & 3) * 4 : ((row >> 1) & 1) * 4; };
+  // chunk e of an operand's slice: k row e / C, logical chunk (e % C) ^ f(row)
+  auto row_of = [&](int i) { return ((int)threadIdx.x + GNTHR * (i < A_LOADS ? i : i - A_LOADS)) / (i < A_LOADS ? CA : CB); };
+  auto col_of = [&](int i) {  // its logical chunk, clamped to the operand's columns
+    const int C = i < A_LOADS ? CA : CB, e = (int)threadIdx.x + GNTHR * (i < A_LOADS ? i : i - A_LOADS);
+    const int last = (i < A_LOADS ? p.M - m0 : p.N - n0) / 8 - 1;
+    return min((e % C) ^ swz(C, e / C), last);
+  };
+  const uint32_t a_row = (uint32_t)(p.lda * 2), b_row = (uint32_t)(p.ldb * 2);
+  uint32_t goff[NL];
 #pragma unroll
-  for (int i = 0; i < NL; ++i) {
-    const bool is_a = i < A_LOADS;
-    const int e = threadIdx.x + GNTHR * (is_a ? i : i - A_LOADS);
-    const int C = is_a ? CA : CB;
-    const int r = e / C, c = e % C;
-    off[i] = (uint32_t)r * (uint32_t)((is_a ? p.lda : p.ldb) * 2) + (uint32_t)c * 16u;
-    lofs[i] = is_a ? r * PA + c * 8 : A_EL + r * PB + c * 8;
-    ok[i] = is_a ? m0 + 8 * c < p.M : n0 + 8 * c < p.N;
-  }
-  u32x4 pre[NL];
-  __amdgpu_buffer_rsrc_t ra, rb;
-  auto rsrcs = [&](int k0) {  // the slice's k rows below ke (rows past it read zero)
-    const uint32_t krows = (uint32_t)max(0, min(GBK, ke - k0));
-    ra = make_rsrc(p.a + (int64_t)k0 * p.lda + m0, krows * (uint32_t)(p.lda * 2));
-    rb = make_rsrc(p.b + (int64_t)k0 * p.ldb + n0, krows * (uint32_t)(p.ldb * 2));
+  for (int i = 0; i < NL; ++i)
+    goff[i] = (uint32_t)row_of(i) * (i < A_LOADS ? a_row : b_row) + (uint32_t)col_of(i) * 16u;
+  // resources over 64 k rows from the range's first (the last row ends with its columns)
+  const u32x4 ra0 = dma_rsrc(p.a + (int64_t)kb * p.lda + m0, GBK * a_row - (uint32_t)m0 * 2u);
+  const u32x4 rb0 = dma_rsrc(p.b + (int64_t)kb * p.ldb + n0, GBK * b_row - (uint32_t)n0 * 2u);
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16*)lds + (uint32_t)wave * 1024u);
+  auto dma = [&](int i, int kt, int buf) {
+    const uint32_t at = lds0 + (uint32_t)buf * (STAGE * 2) +
+                        (i < A_LOADS ? i * (GNTHR * 16) : GBK * BMT * 2 + (i - A_LOADS) * (GNTHR * 16));
+    const uint64_t add = (uint64_t)kt * GBK * (i < A_LOADS ? a_row : b_row);
+    dma_b128(dma_advance(i < A_LOADS ? ra0 : rb0, add), goff[i], 0u, at);
   };
-  auto gload = [&](int i) {
-    pre[i] = __builtin_amdgcn_raw_buffer_load_b128(i < A_LOADS ? ra : rb, ok[i] ? off[i] : 0xFFFFFFF0u, 0, 0);
-  };
-  auto lstore = [&](int i, int buf) { *reinterpret_cast<u32x4*>(lds + buf * STAGE + lofs[i]) = pre[i]; };
 
   floatx16 acc[TN][TM];
 #pragma unroll
@@ -425,102 +423,108 @@ __global__ __launch_bounds__(GNTHR, 1) void gemm_grad_tt_big_kernel(GradArgs p) 
     for (int b = 0; b < TM; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-  auto frag = [&](const bf16* t, int P, int rbase, int ks) {
-    const int row = 16 * ks + 4 * g + (j16 >> 2);
-    const int col = rbase + mbase + 4 * (j16 & 3);
-    const shortx4 lo = lds_read_tr(t + row * P + col);
-    const shortx4 hi = lds_read_tr(t + (row + 8) * P + col);
+  // fragment of the 32 columns of block `blk`: k rows 16 ks + 4 g + (j16 >> 2) and 8 on
+  auto frag = [&](const bf16* t, int C, int blk, int ks) {
+    const int q = j16 >> 2, x = C % 16 == 0 ? q : (q >> 1);
+    const bf16* at = t + (16 * ks + 4 * g + q) * (8 * C) + ((blk ^ x) * 32 + mbase + 4 * (j16 & 3));
+    const shortx4 lo = lds_read_tr(at), hi = lds_read_tr(at + 64 * C);
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
   bf16x8 af[2][TM], wf[2][TN];
   auto fread = [&](int slot, int buf, int ks) {
     const bf16* As = lds + buf * STAGE;
-    const bf16* Bs = As + A_EL;
+    const bf16* Bs = As + GBK * BMT;
 #pragma unroll
-    for (int b = 0; b < TM; ++b) af[slot][b] = frag(As, PA, wm * TM * 32 + 32 * b, ks);
+    for (int b = 0; b < TM; ++b) af[slot][b] = frag(As, CA, wm * TM + b, ks);
 #pragma unroll
-    for (int a = 0; a < TN; ++a) wf[slot][a] = frag(Bs, PB, wn * TN * 32 + 32 * a, ks);
+    for (int a = 0; a < TN; ++a) wf[slot][a] = frag(Bs, CB, wn * TN + a, ks);
   };
-
-  auto slice = [&](int kt, auto st_c, auto ld_c) {
-    constexpr bool ST = decltype(st_c)::value, LD = decltype(ld_c)::value;
-    constexpr int NMF = TM * TN;
-    constexpr int NSPREAD = 3;  // steps that carry the next slice's LDS stores
-    const int b = kt & 1;
-    if (LD) rsrcs(kb + (kt + 2) * GBK);
+  // one slice, as in gemm_bf16_dma_kernel
+  auto slice = [&](int kt, int buf, auto more_c, auto left_c, auto ld_c) {
+    constexpr bool MORE = decltype(more_c)::value, LD = decltype(ld_c)::value;
+    constexpr int LEFT = decltype(left_c)::value, NMF = TM * TN;
+    const int nbuf = buf + 1 == NS ? 0 : buf + 1;
 #pragma unroll
     for (int ks = 0; ks < GBK / 16; ++ks) {
       const int cur = ks & 1;
       if (ks + 1 < GBK / 16) {
-        fread(cur ^ 1, b, ks + 1);
-      } else if (ST) {
-        __syncthreads();
-        fread(cur ^ 1, b ^ 1, 0);
+        fread(cur ^ 1, buf, ks + 1);
+      } else if (MORE) {
+        wait_barrier<LEFT * NL>();
+        fread(cur ^ 1, nbuf, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int j = 0; j < NMF; ++j) {
         const int a = j / TM, bb = j % TM;
         acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[cur][a], af[cur][bb], acc[a][bb], 0, 0, 0);
-        if (ks < NSPREAD && ST) {
+        if (LD && ks + 1 == GBK / 16) {
 #pragma unroll
-          for (int i = (ks * NMF + j) * NL / (NSPREAD * NMF); i < (ks * NMF + j + 1) * NL / (NSPREAD * NMF); ++i) {
-            lstore(i, b ^ 1);
-            if (LD) gload(i);
-          }
+          for (int i = j * NL / NMF; i < (j + 1) * NL / NMF; ++i) dma(i, kt + NS, buf);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
-
-  const int nk = (ke - kb + GBK - 1) / GBK;
+  using yes = std::true_type;
+  using no = std::false_type;
+  using zero = std::integral_constant<int, 0>;
+  const int nk = max(0, ke - kb) / GBK;  // whole slices
   if (nk > 0) {
-    rsrcs(kb);
+    for (int t = 0; t < min(NS, nk); ++t)
 #pragma unroll
-    for (int i = 0; i < NL; ++i) gload(i);
-#pragma unroll
-    for (int i = 0; i < NL; ++i) lstore(i, 0);
-    if (nk > 1) {
-      rsrcs(kb + GBK);
-#pragma unroll
-      for (int i = 0; i < NL; ++i) gload(i);
+      for (int i = 0; i < NL; ++i) dma(i, t, t);
+    if (nk >= NS)
+      wait_barrier<(NS - 1) * NL>();
+    else
+      wait_barrier<0>();
+    fread(0, 0, 0);
+    int kt = 0, buf = 0;
+    for (; kt + NS < nk; ++kt) {
+      slice(kt, buf, yes{}, std::integral_constant<int, NS - 2>{}, yes{});
+      buf = buf + 1 == NS ? 0 : buf + 1;
     }
+    for (; kt + 1 < nk; ++kt) {
+      slice(kt, buf, yes{}, zero{}, no{});
+      buf = buf + 1 == NS ? 0 : buf + 1;
+    }
+    slice(kt, buf, no{}, zero{}, no{});
+  }
+  const int tail = max(0, ke - kb) - nk * GBK;
+  if (tail > 0) {
+    const int k0 = kb + nk * GBK;
+    const __amdgpu_buffer_rsrc_t ta = make_rsrc(p.a + (int64_t)k0 * p.lda + m0, (uint32_t)tail * a_row - (uint32_t)m0 * 2u);
+    const __amdgpu_buffer_rsrc_t tb = make_rsrc(p.b + (int64_t)k0 * p.ldb + n0, (uint32_t)tail * b_row - (uint32_t)n0 * 2u);
+    u32x4 v[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      v[i] = __builtin_amdgcn_raw_buffer_load_b128(i < A_LOADS ? ta : tb, row_of(i) < tail ? goff[i] : 0xFFFFFFF0u, 0, 0);
+    __syncthreads();  // every wave has read its last fragments
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      *reinterpret_cast<u32x4*>(lds + (i < A_LOADS ? i * GNTHR * 8 : GBK * BMT + (i - A_LOADS) * GNTHR * 8) +
+                                threadIdx.x * 8) = v[i];
     __syncthreads();
     fread(0, 0, 0);
-    using yes = std::true_type;
-    using no = std::false_type;
-    int kt = 0;
-    for (; kt + 2 < nk; ++kt) slice(kt, yes{}, yes{});
-    if (kt + 1 < nk) {
-      slice(kt, yes{}, no{});
-      ++kt;
-    }
-    slice(kt, no{}, no{});
+    slice(0, 0, no{}, zero{}, no{});
   }
 
-  // fp32 partial (or the result, unsplit).  The lane holds rows
-  // m = .. + 32 bb + l32 and column groups n = .. + 32 a + 8 r4 + 4 g + {0..3};
-  // stored from there, a store instruction would write 16-byte pieces of 32
-  // rows.  So the tile goes through LDS in two passes of 128 rows (rows
-  // 64 p + [0, 64) of each wave row half) and leaves in whole 16-byte row
-  // chunks, consecutive lanes on consecutive chunks.
+  // fp32 partial (or the result, unsplit), staged through LDS in NP passes (rows
+  // HR pass + [0, HR) of each wave row half) and stored as whole 16-byte row chunks
   float* out = static_cast<float*>(p.out) + (int64_t)blockIdx.z * p.M * p.N;
-  constexpr int SPF = BNB + 4;  // staged row pitch (fp32): a 16-byte pad
-  static_assert(128 * SPF * 4 <= 2 * STAGE * 2, "the staging fits the LDS buffers");
-  constexpr int CPR = BNB / 4, PER = 128 * CPR / GNTHR;
+  constexpr int CPR = BNT / 4, PER = RPP * CPR / GNTHR;
   float* sf = reinterpret_cast<float*>(lds);
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int pass = 0; pass < NP; ++pass) {
     __syncthreads();  // pass 0: the last fragments are read; pass 1: pass 0's rows are read
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < BPP; ++h)
 #pragma unroll
       for (int a = 0; a < TN; ++a)
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-          const floatx16& t = acc[a][2 * pass + h];
-          *reinterpret_cast<float4*>(sf + (wm * 64 + 32 * h + l32) * SPF + wn * TN * 32 + 32 * a + 8 * r4 + 4 * g) =
+          const floatx16& t = acc[a][BPP * pass + h];
+          *reinterpret_cast<float4*>(sf + (wm * HR + 32 * h + l32) * SPF + wn * TN * 32 + 32 * a + 8 * r4 + 4 * g) =
               make_float4(t[4 * r4], t[4 * r4 + 1], t[4 * r4 + 2], t[4 * r4 + 3]);
         }
     __syncthreads();
@@ -528,7 +532,7 @@ __global__ __launch_bounds__(GNTHR, 1) void gemm_grad_tt_big_kernel(GradArgs p) 
     for (int q = 0; q < PER; ++q) {
       const int c = (int)threadIdx.x + GNTHR * q;
       const int sr = c / CPR, cc = c % CPR;
-      const int m = m0 + (sr / 64) * 128 + 64 * pass + sr % 64, n = n0 + 4 * cc;
+      const int m = m0 + (sr / HR) * (BMT / 2) + HR * pass + sr % HR, n = n0 + 4 * cc;
       if (m < p.M && n < p.N)
         *reinterpret_cast<float4*>(out + (int64_t)m * p.N + n) =
             *reinterpret_cast<const float4*>(sf + sr * SPF + 4 * cc);
@@ -536,32 +540,88 @@ __global__ __launch_bounds__(GNTHR, 1) void gemm_grad_tt_big_kernel(GradArgs p) 
   }
 }
 
-// Whether the weight gradient out[M][N] (reduction K, row strides lda, ldb)
-// runs on the large-tile kernel, and with which tile width.
-bool grad_big_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
-  return DSP_GRAD_BIG && M >= 512 && N >= 512 && M % 8 == 0 && N % 8 == 0 && K >= 2048 &&
-         (int64_t)GBK * lda * 2 < (int64_t(1) << 31) && (int64_t)GBK * ldb * 2 < (int64_t(1) << 31) &&
-         M * N < (int64_t(1) << 31);
-}
-int grad_big_tn(int64_t N) { return N >= 2048 ? 4 : 3; }
+// Tile shapes of the weight gradient and their times: a launch of `tiles` *
+// splits work-groups takes full rounds of 256 * levels and one of the rest, with
+// 1 .. levels of them per CU; a round with j per CU takes a[j - 1] + b[j - 1] * (64-row
+// slices) microseconds, and each partial of the reduction a write and a read at
+// about 4 TB/s each.  Values from the shapes named at the kernel.
+struct GradTile {
+  int tm, tn, levels;
+  double a[3], b[3];
+};
+constexpr GradTile kGradTiles[5] = {{2, 3, 2, {4.0, 5.0}, {0.76, 1.30}},
+                                    {2, 2, 2, {3.0, 4.0}, {0.62, 0.98}},
+                                    {2, 2, 1, {4.0}, {0.53}},
+                                    {1, 2, 3, {2.0, 2.5, 3.0}, {0.55, 0.62, 0.98}},
+                                    {1, 1, 2, {2.0, 2.0}, {0.25, 0.42}}};
 
-template <bool TA, bool TB, int EPI>
-int launch_grad(const GradArgs& p0, int splits, float* ws, hipStream_t s) {
-  GradArgs p = p0;
+struct GradChoice {
+  int tile, splits;
+};
+// the fastest tile shape and split count, of at most max_splits
+GradChoice choose_grad(int64_t M, int64_t N, int64_t K, int max_splits) {
+  GradChoice best = {-1, 1};
+  double best_cost = 0.0;
+  const int64_t slices = (K + GBK - 1) / GBK;
+  for (int i = 0; i < 5; ++i) {
+    const GradTile& t = kGradTiles[i];
+    const int64_t tiles = ((M + 64 * t.tm - 1) / (64 * t.tm)) * ((N + 64 * t.tn - 1) / (64 * t.tn));
+    for (int s = 1; s <= max_splits; ++s) {
+      const int64_t per = (slices + s - 1) / s;
+      if (s > 1 && per * (s - 1) >= slices) break;  // the last split would be empty
+      const int64_t wgs = tiles * s, round = 256 * t.levels, rest = wgs % round;
+      double cost = (double)(wgs / round) * (t.a[t.levels - 1] + t.b[t.levels - 1] * (double)per);
+      if (rest) {
+        const int j = (int)((rest + 255) / 256) - 1;
+        cost += t.a[j] + t.b[j] * (double)per;
+      }
+      if (s > 1) cost += 3.0 + (double)s * (double)M * (double)N * 1e-6;
+      if (best.tile < 0 || cost < best_cost) {
+        best = {i, s};
+        best_cost = cost;
+      }
+    }
+  }
+  return best;
+}
+
+int launch_reduce(const float* ws, void* out, int64_t n, int splits, hipStream_t s) {
+  const int64_t n4 = n / 4;
+  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((uint32_t)((n4 + 255) / 256)), dim3(256), 0, s,
+                     reinterpret_cast<const float4*>(ws), static_cast<float4*>(out), n4, splits);
+  return last_launch_status();
+}
+
+int launch_grad_tt(GradArgs p, int max_splits, float* ws, hipStream_t s) {
+  const GradChoice c = choose_grad(p.M, p.N, p.K, ws ? max_splits : 1);
+  const GradTile& t = kGradTiles[c.tile];
+  const int64_t n_nt = (p.N + 64 * t.tn - 1) / (64 * t.tn), tiles = ((p.M + 64 * t.tm - 1) / (64 * t.tm)) * n_nt;
+  if (tiles >= (int64_t(1) << 31)) return DSP_ERR_SHAPE;
+  p.n_ntiles = (int)n_nt;
+  p.n_tiles = (int)tiles;
+  p.k_per_split = ((p.K + GBK - 1) / GBK + c.splits - 1) / c.splits * GBK;
+  void* out = p.out;
+  if (c.splits > 1) p.out = ws;
+  const dim3 grid((uint32_t)tiles, 1, (uint32_t)c.splits), block(GNTHR);
+  switch (c.tile) {
+    case 0: hipLaunchKernelGGL((gemm_grad_tt_dma_kernel<2, 3, 2, 2>), grid, block, 0, s, p); break;
+    case 1: hipLaunchKernelGGL((gemm_grad_tt_dma_kernel<2, 2, 2, 2>), grid, block, 0, s, p); break;
+    case 2: hipLaunchKernelGGL((gemm_grad_tt_dma_kernel<2, 2, 4, 1>), grid, block, 0, s, p); break;
+    case 3: hipLaunchKernelGGL((gemm_grad_tt_dma_kernel<1, 2, 2, 3>), grid, block, 0, s, p); break;
+    default: hipLaunchKernelGGL((gemm_grad_tt_dma_kernel<1, 1, 4, 2>), grid, block, 0, s, p); break;
+  }
+  const int st = last_launch_status();
+  if (st != DSP_OK || c.splits == 1) return st;
+  return launch_reduce(ws, out, (int64_t)p.M * p.N, c.splits, s);
+}
+
+template <int EPI>
+int launch_grad(GradArgs p, hipStream_t s) {
   const int64_t n_mt = (p.M + GBM - 1) / GBM, n_nt = (p.N + GBN - 1) / GBN;
   const int64_t tiles = n_mt * n_nt;
   p.n_ntiles = (int)n_nt;
   p.n_tiles = (int)tiles;
-  p.k_per_split = ((p.K + splits - 1) / splits + GBK - 1) / GBK * GBK;
-  void* final_out = p.out;
-  if (splits > 1) p.out = ws;
-  hipLaunchKernelGGL((gemm_grad_kernel<TA, TB, EPI>), dim3((uint32_t)tiles, 1, (uint32_t)splits), dim3(GNTHR),
-                     0, s, p);
-  int st = last_launch_status();
-  if (st != DSP_OK || splits == 1) return st;
-  const int64_t n4 = (int64_t)p.M * p.N / 4;
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((uint32_t)((n4 + 255) / 256)), dim3(256), 0, s,
-                     reinterpret_cast<const float4*>(ws), reinterpret_cast<float4*>(final_out), n4, splits);
+  hipLaunchKernelGGL((gemm_grad_kernel<EPI>), dim3((uint32_t)tiles), dim3(GNTHR), 0, s, p);
   return last_launch_status();
 }
 
@@ -590,45 +650,25 @@ int launch_colsum_f32(const float* dy, float* db, int64_t M, int N, hipStream_t 
   return last_launch_status();
 }
 
+// The partials a caller's workspace provides for (the launch takes as many as it
+// needs of them): the split count minimising rounds of work-groups times slices per
+// split plus the extra partials' write and read, with at least 32 slices per split
+// (so a reduction of fewer than 4096 runs without a workspace).
 int grad_splits(int64_t M, int64_t N, int64_t K) {
-  if (grad_big_ok(M, N, K, M, N)) {
-    // the large-tile kernel: one work-group per CU (256 slots), in units of
-    // one 64-wide slice of a tile on a full round; a split's extra fp32
-    // partial (8 M N bytes at 5 TB/s) against ~2 us per slice round
-    const int bnb = grad_big_tn(N) * 64;
-    const int64_t tiles = ((M + GB_BM - 1) / GB_BM) * ((N + bnb - 1) / bnb);
-    const int64_t slices = (K + GBK - 1) / GBK;
-    const double per_split = (double)M * (double)N * 8e-7;
-    int best = 1;
-    double best_cost = 0.0;
-    for (int s = 1; s <= 16; ++s) {
-      const int64_t per = (slices + s - 1) / s;
-      if (per < 32 || per * (s - 1) >= slices) break;
-      const int64_t rounds = (tiles * s + 255) / 256;
-      const double cost = (double)rounds * (double)(per + 2) + (s > 1 ? s * per_split : 0.0);
-      if (s == 1 || cost < best_cost) {
-        best = s;
-        best_cost = cost;
-      }
-    }
-    return best;
-  }
-  // The split count minimising a cost model, in units of one 64-wide K slice
-  // of one tile on a full round of work-groups (two per CU, 256 CUs):
-  //   rounds * (slices per split + 2 for the work-group's set-up and fp32
-  //   store) + s * (the extra write and read of an M x N fp32 partial,
-  //   about 8 M N bytes at 5 TB/s against 2.9 us per slice round).
-  // Splits keep at least 32 slices (a reduction of 2048), so small problems
-  // run unsplit.
-  const int64_t tiles = ((M + GBM - 1) / GBM) * ((N + GBN - 1) / GBN);
+  const bool big = M >= 512 && N >= 512 && M % 8 == 0 && N % 8 == 0 && K >= 2048 &&
+                   (int64_t)GBK * M * 2 < (int64_t(1) << 31) && (int64_t)GBK * N * 2 < (int64_t(1) << 31) &&
+                   M * N < (int64_t(1) << 31);
+  const int bn = !big ? 128 : N >= 2048 ? 256 : 192;
+  const int64_t slots = big ? 256 : 512;
+  const int64_t tiles = ((M + 255) / 256) * ((N + bn - 1) / bn);
   const int64_t slices = (K + GBK - 1) / GBK;
-  const double per_split = (double)M * (double)N * 5.5e-7;
+  const double per_split = (double)M * (double)N * (big ? 8e-7 : 5.5e-7);
   int best = 1;
   double best_cost = 0.0;
   for (int s = 1; s <= 16; ++s) {
     const int64_t per = (slices + s - 1) / s;
     if (per < 32 || per * (s - 1) >= slices) break;  // too short, or the last split empty
-    const int64_t rounds = (tiles * s + 511) / 512;
+    const int64_t rounds = (tiles * s + slots - 1) / slots;
     const double cost = (double)rounds * (double)(per + 2) + (s > 1 ? s * per_split : 0.0);
     if (s == 1 || cost < best_cost) {
       best = s;
@@ -658,45 +698,15 @@ int launch_gemm_grad(const void* a, int ta, int64_t lda, const void* b, int tb, 
   p.M = (int)M;
   p.N = (int)N;
   p.K = (int)K;
-  if (ta == 1 && tb == 1 && epi == DSP_GRAD_EPI_F32 && grad_big_ok(M, N, K, lda, ldb) &&
-      (splits == 1 || ws)) {
-    const int tn = grad_big_tn(N);
-    const int bnb = tn * 64;
-    const int64_t n_nt = (N + bnb - 1) / bnb;
-    const int64_t tiles = ((M + GB_BM - 1) / GB_BM) * n_nt;
-    p.n_ntiles = (int)n_nt;
-    p.n_tiles = (int)tiles;
-    p.k_per_split = ((p.K + splits - 1) / splits + GBK - 1) / GBK * GBK;
-    if (splits > 1) p.out = ws;
-    if (tn == 4)
-      hipLaunchKernelGGL((gemm_grad_tt_big_kernel<4>), dim3((uint32_t)tiles, 1, (uint32_t)splits), dim3(GNTHR), 0, s,
-                         p);
-    else
-      hipLaunchKernelGGL((gemm_grad_tt_big_kernel<3>), dim3((uint32_t)tiles, 1, (uint32_t)splits), dim3(GNTHR), 0, s,
-                         p);
-    int st = last_launch_status();
-    if (st != DSP_OK || splits == 1) return st;
-    const int64_t n4 = M * N / 4;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((uint32_t)((n4 + 255) / 256)), dim3(256), 0, s,
-                       reinterpret_cast<const float4*>(ws), reinterpret_cast<float4*>(out), n4, splits);
-    return last_launch_status();
+  if (ta == 1 && tb == 1) return epi == DSP_GRAD_EPI_F32 ? launch_grad_tt(p, splits, ws, s) : DSP_ERR_ARG;
+  if (ta != 0 || tb != 1 || splits != 1) return DSP_ERR_ARG;  // the gradients' other layout
+  switch (epi) {
+    case DSP_GRAD_EPI_F32: return launch_grad<DSP_GRAD_EPI_F32>(p, s);
+    case DSP_GRAD_EPI_BF16: return launch_grad<DSP_GRAD_EPI_BF16>(p, s);
+    case DSP_GRAD_EPI_GELU_BWD: return launch_grad<DSP_GRAD_EPI_GELU_BWD>(p, s);
+    case DSP_GRAD_EPI_RELU_BWD: return launch_grad<DSP_GRAD_EPI_RELU_BWD>(p, s);
+    default: return DSP_ERR_ARG;
   }
-#define DSP_GRAD_CASE(TA_, TB_)                                                                    \
-  if (ta == TA_ && tb == TB_) {                                                                   \
-    switch (epi) {                                                                                \
-      case DSP_GRAD_EPI_F32: return launch_grad<TA_, TB_, DSP_GRAD_EPI_F32>(p, splits, ws, s);    \
-      case DSP_GRAD_EPI_BF16: return launch_grad<TA_, TB_, DSP_GRAD_EPI_BF16>(p, 1, ws, s);       \
-      case DSP_GRAD_EPI_GELU_BWD: return launch_grad<TA_, TB_, DSP_GRAD_EPI_GELU_BWD>(p, 1, ws, s); \
-      case DSP_GRAD_EPI_RELU_BWD: return launch_grad<TA_, TB_, DSP_GRAD_EPI_RELU_BWD>(p, 1, ws, s); \
-      default: return DSP_ERR_ARG;                                                                \
-    }                                                                                             \
-  }
-  DSP_GRAD_CASE(0, 1)
-  DSP_GRAD_CASE(1, 1)
-  DSP_GRAD_CASE(0, 0)
-  DSP_GRAD_CASE(1, 0)
-#undef DSP_GRAD_CASE
-  return DSP_ERR_ARG;
 }
 
 // 16 columns per work-group (G = 2), or 32 where that still gives every second
