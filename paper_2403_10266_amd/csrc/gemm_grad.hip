@@ -278,14 +278,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float4* __rest
 // and the caller lends no scratch for partial sums.  So one work-group of 1024
 // threads takes G 16-byte chunks (bf16: 8 columns each; fp32: one column per
 // thread, as rows need no alignment there) of every row: G threads on a row,
-// 1024 / G rows at a time, four loads of each thread in flight.  The rows' sums
+// 1024 / G rows at a time, eight loads of each thread in flight.  The rows' sums
 // then meet in a fixed tree (lanes, then waves in order): deterministic, and a
 // shorter chain of fp32 adds than a walk down the column.
-//   13600 bf16 rows of 1152 / 3456 / 4608 columns: 24 / 25 / 31 us (1.3 / 3.7 /
+//   13600 bf16 rows of 1152 / 3456 / 4608 columns: 24 / 25 / 31 us with four loads in
+// flight, about 6 less with eight (1.3 / 3.7 /
 // 4.0 TB/s), where one thread walking down 4 columns (two to five work-groups on
 // the chip, one load in flight each) took 3750 / 3720 / 3570 us; 2048 fp32 rows
 // 470 -> 5-11 us.
-constexpr int CS_THREADS = 1024, CS_UNROLL = 4;
+constexpr int CS_THREADS = 1024, CS_UNROLL = 8;
 
 template <bool BF, int G>
 __global__ __launch_bounds__(CS_THREADS) void colsum_kernel(const void* __restrict__ dyp, float* db, int64_t M, int N) {
