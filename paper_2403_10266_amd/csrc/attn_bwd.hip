@@ -29,7 +29,7 @@
 //    bf16, with the same permuted row order on both sides.  The last 16 rows
 //    of a head width that is not a multiple of 32 run on 16x16x32 MFMAs.
 //
-// fp32 path: plain FMA loops, one thread per (unit, row, 32-column slice).
+// The fp32 path is in attn_f32.hip.
 #include <math.h>
 
 #include <algorithm>
@@ -892,8 +892,61 @@ void fill_common(P& p, const AttnBwdArgs& a) {
   p.delta = a.delta;
 }
 
+// Waves (32 rows each) per work-group of the dQ and dK/dV kernels: 4 or 8, two
+// work-groups of 8 or three of 4 on a CU.  8 read the other side's tiles for twice the
+// rows; 4 leave fewer CUs idle where the launch is a few rounds or the rows end early
+// in a block.  `rows` owned rows per unit against `tiles` tiles of 64: full rounds of
+// 256 * levels work-groups and one of the rest, with 1 .. levels per CU, at a[j - 1] +
+// b[j - 1] * tiles microseconds a round, fitted to 71 shapes of self-attention (D = 72, 16
+// to 640 units, 150 to 3000 rows, both kernels together, relative error 5-7%).  Choosing
+// by it is within 0.3% of the better one on average and takes 9% off what 8 waves
+// need: 34 frames of 400 tokens (16 heads) 194 -> 165 us, 7 x 1350 290 -> 270, 16 units of
+// 1024 67 -> 54; 640 units of 1024 stay on 8.
+int bwd_waves(int64_t units, int64_t rows, int64_t tiles) {
+  struct Shape {
+    int waves, levels;
+    double first, a[3], b[3];
+  };
+  constexpr Shape shapes[2] = {{8, 2, 0.0, {13.3, 27.6}, {3.62, 7.69}}, {4, 3, 11.6, {0.1, 8.1, 11.5}, {2.73, 3.89, 6.47}}};
+  double cost[2];
+  for (int i = 0; i < 2; ++i) {
+    const Shape& q = shapes[i];
+    const int64_t blocks = units * ((rows + 32 * q.waves - 1) / (32 * q.waves)), round = 256 * q.levels,
+                  rest = blocks % round;
+    cost[i] = q.first + (double)(blocks / round) * (q.a[q.levels - 1] + q.b[q.levels - 1] * (double)tiles);
+    if (rest) {
+      const int j = (int)((rest + 255) / 256) - 1;
+      cost[i] += q.a[j] + q.b[j] * (double)tiles;
+    }
+  }
+  return cost[1] < cost[0] ? 4 : 8;
+}
+
 template <int D, int NW>
-int launch_bwd_nw(const AttnBwdArgs& a, hipStream_t s) {
+int launch_dq(BwdParams p, const AttnBwdArgs& a, hipStream_t s) {
+  // query heads x blocks of 32 NW queries
+  const int64_t nq = (a.L + 32 * NW - 1) / (32 * NW), blocks = a.B * a.X * a.H * nq;
+  if (blocks >= (int64_t(1) << 31)) return DSP_ERR_SHAPE;
+  p.n_blk = (uint32_t)nq;
+  p.n_blocks = (uint32_t)blocks;
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW>), dim3((uint32_t)blocks), dim3(NW * 64), 0, s, p);
+  return last_launch_status();
+}
+
+template <int D, int NW>
+int launch_dkv(BwdParams p, const AttnBwdArgs& a, hipStream_t s) {
+  // key/value heads x blocks of 32 NW keys
+  const int64_t nk = (a.Lk + 32 * NW - 1) / (32 * NW), blocks = a.B * a.X * a.Hkv * nk;
+  if (blocks >= (int64_t(1) << 31)) return DSP_ERR_SHAPE;
+  p.n_blk = (uint32_t)nk;
+  p.n_blocks = (uint32_t)blocks;
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, NW>), dim3((uint32_t)blocks), dim3(NW * 64), 0, s, p);
+  return last_launch_status();
+}
+
+// dQ, then dK and dV, with nwq and nwk waves per work-group
+template <int D>
+int launch_bwd_two(const AttnBwdArgs& a, int nwq, int nwk, hipStream_t s) {
   BwdParams p;
   p.q = static_cast<const bf16*>(a.q);
   p.k = static_cast<const bf16*>(a.k);
@@ -911,23 +964,10 @@ int launch_bwd_nw(const AttnBwdArgs& a, hipStream_t s) {
   p.grp = (uint32_t)(a.H / a.Hkv);
   p.c = a.scale * kLog2e;
   p.scale = a.scale;
-  // dQ: query heads x blocks of 32 NW queries
-  const int64_t nq = (a.L + 32 * NW - 1) / (32 * NW);
-  const int64_t bq = a.B * a.X * a.H * nq;
-  if (bq == 0) return DSP_OK;
-  p.n_blk = (uint32_t)nq;
-  p.n_blocks = (uint32_t)bq;
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW>), dim3((uint32_t)bq), dim3(NW * 64), 0, s, p);
-  int st = last_launch_status();
-  if (st != DSP_OK) return st;
-  // dK, dV: key/value heads x blocks of 32 NW keys
-  const int64_t nk = (a.Lk + 32 * NW - 1) / (32 * NW);
-  const int64_t bk = a.B * a.X * a.Hkv * nk;
-  if (bk == 0) return DSP_OK;
-  p.n_blk = (uint32_t)nk;
-  p.n_blocks = (uint32_t)bk;
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, NW>), dim3((uint32_t)bk), dim3(NW * 64), 0, s, p);
-  return last_launch_status();
+  if (a.B * a.X * a.L == 0) return DSP_OK;
+  int st = nwq == 2 ? launch_dq<D, 2>(p, a, s) : nwq == 4 ? launch_dq<D, 4>(p, a, s) : launch_dq<D, 8>(p, a, s);
+  if (st != DSP_OK || a.Lk == 0) return st;
+  return nwk == 2 ? launch_dkv<D, 2>(p, a, s) : nwk == 4 ? launch_dkv<D, 4>(p, a, s) : launch_dkv<D, 8>(p, a, s);
 }
 
 template <int D, int NW>
@@ -980,9 +1020,11 @@ int launch_bwd_d(const AttnBwdArgs& a, hipStream_t s) {
     return launch_bwd_short<D, 4>(a, s);
   }
 #endif
-  if (L <= 64) return launch_bwd_nw<D, 2>(a, s);
-  if (L <= 128) return launch_bwd_nw<D, 4>(a, s);
-  return launch_bwd_nw<D, 8>(a, s);
+  if (L <= 64) return launch_bwd_two<D>(a, 2, 2, s);
+  if (L <= 128) return launch_bwd_two<D>(a, 4, 4, s);
+  const int64_t bx = a.B * a.X;
+  return launch_bwd_two<D>(a, bwd_waves(bx * a.H, a.L, (a.Lk + 63) / 64),
+                           bwd_waves(bx * a.Hkv, a.Lk, (a.H / a.Hkv) * ((a.L + 63) / 64)), s);
 }
 
 }  // namespace

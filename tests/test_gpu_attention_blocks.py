@@ -36,3 +36,22 @@ def test_query_blocks(B, X, Lq, Lk, H, Hkv, D):
         grads = dsp.dsp_attn_general_bwd(qd, kd, vd, o, dev(do, "bf16"), lse, H, Hkv)
         for got, w, name in zip(grads, oracle.attention_grouped_bwd(q, k, v, do, H, Hkv), ("dq", "dk", "dv")):
             _grad_close(host(got), w, "bf16", name)
+
+
+@pytest.mark.parametrize("B,X,Lq,Lk,H,Hkv,D", [
+    (1, 2, 129, 257, 2, 2, 72),     # both kernels on 4 waves
+    (1, 34, 400, 130, 16, 16, 16),  # 544 units of 400 queries (4 waves), 130 keys
+    (1, 40, 256, 150, 16, 16, 16),  # 640 units of exactly one 8-wave query block
+    (1, 7, 300, 140, 8, 2, 64),     # grouped heads: fewer dK/dV work-groups
+])
+def test_backward_waves(B, X, Lq, Lk, H, Hkv, D):
+    import paper_2403_10266_amd as dsp
+    rng = np.random.default_rng(Lq + 3 * Lk + D)
+    q, do = (synth.bf16_round(rng.standard_normal((B, X, Lq, H * D), dtype=np.float32)) for _ in range(2))
+    k, v = (synth.bf16_round(rng.standard_normal((B, X, Lk, Hkv * D), dtype=np.float32)) for _ in range(2))
+    say(f"backward waves B={B} X={X} Lq={Lq} Lk={Lk} H={H} Hkv={Hkv} D={D}")
+    qd, kd, vd = (dev(a, "bf16") for a in (q, k, v))
+    o, lse = dsp.dsp_attn_general(qd, kd, vd, H, Hkv, with_lse=True)
+    grads = dsp.dsp_attn_general_bwd(qd, kd, vd, o, dev(do, "bf16"), lse, H, Hkv)
+    for got, w, name in zip(grads, oracle.attention_grouped_bwd(q, k, v, do, H, Hkv), ("dq", "dk", "dv")):
+        _grad_close(host(got), w, "bf16", name)
