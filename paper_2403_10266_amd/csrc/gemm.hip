@@ -1118,30 +1118,32 @@ int launch_transpose_bf16_batch(const void* const* x, void* const* y, const int6
 // per CU; a round with j tiles per CU is a[j - 1] + b[j - 1] * (K / 64)
 // microseconds.  The numbers are a least-squares fit (relative error 9%) to 95
 // measured shapes, M = 64 .. 32768, (N, K) the linear maps of widths 1152 and 2048;
-// choosing by them costs 1.2% on average against each shape's best.  The register-
-// staged 256 x 256 and 256 x 192 tiles win where many full rounds meet a long K
-// (8000 x 2048 x 8192: 220 against 256 us, 32768 x 4608 x 1152 + GELU: equal), the
-// 128-row tiles below that.
+// choosing by them costs 1.2% on average against each shape's best.  `act` is what GELU
+// adds to a round (counted for the plain GELU only): on one work-group per CU it
+// stands alone, with two it runs under the other's MFMAs.  The register-staged 256 x
+// 256 and 256 x 192 tiles win where many full rounds meet a long K (8000 x 2048 x
+// 8192: 220 against 256 us), the 128-row tiles below that and with GELU (32768 x 4608 x
+// 1152: 365 against 396 us).
 enum { T_BIG256 = 0, T_BIG192, T_128x192, T_128x128, T_128x128_DEEP, T_64x128, T_64x64, T_COUNT };
 struct TileShape {
   int bm, bn, levels;
-  double a[3], b[3];
+  double a[3], b[3], act;
 };
 constexpr TileShape kTiles[T_COUNT] = {
-    {256, 256, 1, {6.1}, {1.63}},
-    {256, 192, 1, {13.4}, {1.10}},
-    {128, 192, 2, {4.4, 4.5}, {0.68, 1.30}},
-    {128, 128, 2, {1.6, 2.9}, {0.59, 0.96}},
-    {128, 128, 1, {3.7}, {0.50}},
-    {64, 128, 3, {0.1, 2.1, 1.8}, {0.50, 0.58, 0.94}},
-    {64, 64, 2, {1.8, 0.9}, {0.23, 0.40}},
+    {256, 256, 1, {6.1}, {1.63}, 5.8},
+    {256, 192, 1, {13.4}, {1.10}, 4.5},
+    {128, 192, 2, {4.4, 4.5}, {0.68, 1.30}, 2.0},
+    {128, 128, 2, {1.6, 2.9}, {0.59, 0.96}, 2.0},
+    {128, 128, 1, {3.7}, {0.50}, 2.0},
+    {64, 128, 3, {0.1, 2.1, 1.8}, {0.50, 0.58, 0.94}, 1.0},
+    {64, 64, 2, {1.8, 0.9}, {0.23, 0.40}, 0.7},
 };
 
 int64_t tile_count(const TileShape& t, int64_t M, int64_t N) {
   return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
 }
 
-int choose_tiles(int64_t M, int64_t N, int64_t K) {
+int choose_tiles(int64_t M, int64_t N, int64_t K, bool act) {
   int best = -1;
   double best_cost = 0.0;
   const double slices = (double)(K / BK);
@@ -1150,10 +1152,11 @@ int choose_tiles(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = tile_count(t, M, N), round = 256 * t.levels;
     if (i <= T_BIG192 && (tiles < 256 || (i == T_BIG256) != (N >= 2048))) continue;
     const int64_t rest = tiles % round;
-    double cost = (double)(tiles / round) * (t.a[t.levels - 1] + t.b[t.levels - 1] * slices);
+    const double extra = act ? t.act : 0.0;
+    double cost = (double)(tiles / round) * (t.a[t.levels - 1] + t.b[t.levels - 1] * slices + extra);
     if (rest) {
       const int j = (int)((rest + 255) / 256) - 1;
-      cost += t.a[j] + t.b[j] * slices;
+      cost += t.a[j] + t.b[j] * slices + extra;
     }
     if (best < 0 || cost < best_cost) {
       best = i;
@@ -1168,14 +1171,14 @@ int choose_tiles(int64_t M, int64_t N, int64_t K) {
 // pipelined tiles load whole K slices.  K not a multiple of 64: the register-
 // staged large tiles, which mask the tail, where they fill every CU; -1: the
 // 256 x 128 kernel, which takes anything.
-int tile_shape(int64_t M, int64_t N, int64_t K) {
+int tile_shape(int64_t M, int64_t N, int64_t K, bool act) {
   if (!DSP_GEMM_BIG || N % 8 || (int64_t)BIG_BM * N * 4 >= (int64_t(1) << 31)) return -1;
-  if (K % BK == 0) return choose_tiles(M, N, K);
+  if (K % BK == 0) return choose_tiles(M, N, K, act);
   const int big = N >= 2048 ? T_BIG256 : T_BIG192;
   return tile_count(kTiles[big], M, N) >= 256 ? big : -1;
 }
 
-bool linear_bf16_tiled(int64_t M, int64_t N, int64_t K) { return tile_shape(M, N, K) >= 0; }
+bool linear_bf16_tiled(int64_t M, int64_t N, int64_t K) { return tile_shape(M, N, K, false) >= 0; }
 
 int launch_linear_bf16(const void* a, const void* w, const void* bias, const float* residual,
                        void* out, int64_t M, int N, int K, int epilogue, hipStream_t s, void* pre, RowSwap rs) {
@@ -1196,7 +1199,7 @@ int launch_linear_bf16(const void* a, const void* w, const void* bias, const flo
   const bf16* Wt = static_cast<const bf16*>(w);
   const bf16* bs = static_cast<const bf16*>(bias);
   bf16* pb = static_cast<bf16*>(pre);
-  const int shape = tile_shape(M, N, K);
+  const int shape = tile_shape(M, N, K, epilogue == DSP_EPI_GELU && !keep);
   const int64_t st_tiles = shape < 0 ? tiles : tile_count(kTiles[shape], M, N);
   const int64_t st_nt = shape < 0 ? n_nt : (N + kTiles[shape].bn - 1) / kTiles[shape].bn;
   if (st_tiles >= (int64_t(1) << 31)) return DSP_ERR_SHAPE;
