@@ -9,8 +9,16 @@
 // work-group loads its rows and the weights in one round trip, keeps every
 // intermediate in LDS, and writes the sublayer's output rows -- in (B, S, T)
 // order for the spatial half, which performs the Switch on the way out.
-// Arithmetic is fp32 FMA with expf (as the fp32 path's kernels), the softmax
+// Arithmetic is fp32 (products on v_mfma_f32_16x16x4_f32 or FMAs, expf), the softmax
 // two-pass with the exact row maximum.
+//   Bound by latency: one group is a few microseconds on one CU.  The two
+// projections run on the matrix instruction, a 16 x 16 tile per wave, because with one
+// thread per output column their LDS reads (five 16-byte reads per 16 FMAs) took
+// half the kernel's time; a (head, query) task of the attention is shared by 4
+// lanes, each with every fourth key, because at these sizes there are fewer tasks than
+// threads.  Tiny chain (4 groups of 16, then 16 of 4, C = 64): 12.0 + 7.9 -> 9.2 + 7.3 us
+// in a kernel trace; 16 groups of 64, then 64 of 16: 70 -> 39 us a call, 14 of 40 and 80 of
+// 7: 30.5 -> 23.7.
 #include <math.h>
 
 #include "dsp_internal.h"
@@ -19,8 +27,11 @@ namespace dsp {
 namespace {
 
 constexpr int CH_CMAX = 64, CH_LMAX = 64;
-// LDS floats for the largest shape: rows, W_qkv (pitch C + 4), qkv (pitch 3C + 4)
-constexpr int CH_LDS = CH_LMAX * CH_CMAX + 3 * CH_CMAX * (CH_CMAX + 4) + CH_LMAX * (3 * CH_CMAX + 4);
+constexpr int CH_SPLIT = 4;  // lanes per (head, query) task
+// LDS floats for the largest shape: rows (pitch C + 4), W_qkv (pitch C + 4), qkv (pitch 3C + 4)
+constexpr int CH_LDS = CH_LMAX * (CH_CMAX + 4) + 3 * CH_CMAX * (CH_CMAX + 4) + CH_LMAX * (3 * CH_CMAX + 4);
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 
 struct ChainParams {
   const float* x;  // group g's row r at x + (g * L + r) * C
@@ -35,47 +46,52 @@ struct ChainParams {
   RowSwap rs;
 };
 
-// out[m][n] = b[n] + sum_k a[m][k] w[n][k] for rows [m0, m1) of one output
-// column n: float4 chunks of the weight row and of four activation rows at a
-// time (the activation reads are broadcasts), four independent accumulators
+// out[m][n] = b[n] + sum_k a[m][k] w[n][k] for all m < M, n < N, in 16 x 16 tiles, one
+// wave each: lane (i, c) = (lane % 16, lane / 16) reads 4 reduction indices 16 j + 4 c
+// of row i of both operands at a time, which feed 4 MFMAs.  k16: the reduction in
+// steps of 16, zero-padded in both operands.  Tiles past M or N read LDS that holds
+// something else, into outputs that are not stored.
 template <typename Store>
-__device__ __forceinline__ void chain_gemm_col(const float* a, int C, const float* wrow, float b, int m0, int m1,
-                                               Store store) {
-  for (int m = m0; m < m1; m += 4) {
-    const int mr[4] = {m, min(m + 1, m1 - 1), min(m + 2, m1 - 1), min(m + 3, m1 - 1)};
-    float acc[4] = {b, b, b, b};
-#pragma unroll 2
-    for (int k = 0; k < C; k += 4) {
-      const float4 w = *reinterpret_cast<const float4*>(wrow + k);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float4 xv = *reinterpret_cast<const float4*>(a + mr[r] * C + k);
-        acc[r] = fmaf(xv.x, w.x, acc[r]);
-        acc[r] = fmaf(xv.y, w.y, acc[r]);
-        acc[r] = fmaf(xv.z, w.z, acc[r]);
-        acc[r] = fmaf(xv.w, w.w, acc[r]);
-      }
+__device__ __forceinline__ void chain_gemm(const float* a, const float* w, int pitch, int k16, const float* bias, int M,
+                                           int N, int n_waves, Store store) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = lane & 15, c = lane >> 4;
+  const int nt = (N + 15) / 16, tiles = ((M + 15) / 16) * nt;
+  for (int tile = wave; tile < tiles; tile += n_waves) {
+    const int m0 = tile / nt * 16, n0 = tile % nt * 16;
+    const int n = n0 + i;
+    const float b = bias && n < N ? bias[n] : 0.0f;
+    const float* ar = a + (m0 + i) * pitch + 4 * c;
+    const float* wr = w + (n0 + i) * pitch + 4 * c;
+    floatx4 acc = {b, b, b, b};
+    for (int j = 0; j < k16; ++j) {
+      const float4 x = *reinterpret_cast<const float4*>(ar + 16 * j), y = *reinterpret_cast<const float4*>(wr + 16 * j);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, y.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, y.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, y.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, y.w, acc, 0, 0, 0);
     }
+    // the lane holds rows m0 + 4 c + {0..3} of column n
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (m + r < m1) store(m + r, acc[r]);  // rows past m1 recomputed the last one
+      if (m0 + 4 * c + r < M && n < N) store(m0 + 4 * c + r, n, acc[r]);
   }
 }
 
-// NTH threads: 1024 for head widths up to 32 (more threads for the two
-// GEMMs' output columns and row bands; the attention's per-thread registers
-// still fit), 256 for 64
+// NTH threads: 1024 for head widths up to 32 (more waves for the two GEMMs' tiles
+// and more tasks at once; the attention's per-thread registers still fit), 256 for 64
 template <int DT, int NTH>
 __global__ __launch_bounds__(NTH) void chain_sublayer_f32_kernel(ChainParams p) {
   const int L = p.L, C = p.C, H = p.H;
   constexpr int D = DT;
   constexpr int CH_NT = NTH;
   const int C3 = 3 * C;
-  const int WP = C + 4;     // weight row pitch (floats): float4 rows
-  const int QP = C3 + 4;    // qkv row pitch: float4 rows
+  const int k16 = (C + 15) / 16;
+  const int WP = 16 * k16 + 4;  // pitch of the rows and the weights (floats): float4 rows
+  const int QP = C3 + 4;        // qkv row pitch: float4 rows
   __shared__ __attribute__((aligned(16))) float smem[CH_LDS];
-  float* xs = smem;                 // [L][C]: the input rows, later the attention output
-  float* ws = xs + L * C;           // [3C][WP]: W_qkv, later W_o
+  float* xs = smem;                 // [L][WP]: the input rows, later the attention output
+  float* ws = xs + L * WP;          // [3C][WP]: W_qkv, later W_o
   float* qs = ws + C3 * WP;         // [L][QP]: q | k | v
   const int t = threadIdx.x;
   const int64_t row0 = (int64_t)blockIdx.x * L;
@@ -97,41 +113,44 @@ __global__ __launch_bounds__(NTH) void chain_sublayer_f32_kernel(ChainParams p) 
 #pragma unroll
   for (int i = 0; i < WO4; ++i)
     wo4[i] = *reinterpret_cast<const float4*>(p.wo + min(4 * (t + i * CH_NT), no - 4));
-  // weight chunk at element e (4 floats of one row) into LDS row e / C
-  auto wstore = [&](int e, float4 v) { *reinterpret_cast<float4*>(ws + (e / C) * WP + e % C) = v; };
+  // chunk at element e (4 floats of one row) of a matrix into its LDS row e / C
+  auto put = [&](float* base, int e, float4 v) { *reinterpret_cast<float4*>(base + (e / C) * WP + e % C) = v; };
+  // the reduction's padding, C % 16 columns of zeros in the rows and the weights
+  // (W_o takes rows of W_qkv, whose padding it keeps)
+  if (C % 16)
+    for (int r = t; r < L + C3; r += CH_NT)
+      for (int c = C; c < 16 * k16; ++c) xs[r * WP + c] = 0.0f;
 #pragma unroll
   for (int i = 0; i < X4; ++i) {
     const int e = 4 * (t + i * CH_NT);
-    if (e < nx) *reinterpret_cast<float4*>(xs + e) = xr[i];
+    if (e < nx) put(xs, e, xr[i]);
   }
 #pragma unroll
   for (int i = 0; i < WQ4; ++i) {
     const int e = 4 * (t + i * CH_NT);
-    if (e < nq) wstore(e, wq[i]);
+    if (e < nq) put(ws, e, wq[i]);
   }
   __syncthreads();
 
-  // ---- qkv = x W_qkv + b_qkv: thread -> one output column for a band of rows
-  {
-    const int bands = CH_NT / C3;
-    const int n = t % C3, band = t / C3;
-    if (band < bands) {
-      const int rows = (L + bands - 1) / bands;
-      chain_gemm_col(xs, C, ws + n * WP, p.bqkv ? p.bqkv[n] : 0.0f, band * rows, min(L, (band + 1) * rows),
-                     [&](int m, float v) { qs[m * QP + n] = v; });
-    }
-  }
+  // ---- qkv = x W_qkv + b_qkv
+  chain_gemm(xs, ws, WP, k16, p.bqkv, L, C3, CH_NT / 64, [&](int m, int n, float v) { qs[m * QP + n] = v; });
   __syncthreads();
 
   // ---- W_o into LDS (the W_qkv rows are no longer read)
 #pragma unroll
   for (int i = 0; i < WO4; ++i) {
     const int e = 4 * (t + i * CH_NT);
-    if (e < no) wstore(e, wo4[i]);
+    if (e < no) put(ws, e, wo4[i]);
   }
-  // ---- attention per (head, query) task: scores against the L keys, exact
-  // row maximum, exp, row sum, probability-weighted values; output into xs
-  for (int task = t; task < H * L; task += CH_NT) {
+  // ---- attention per (head, query) task: scores against the L keys, exact row
+  // maximum, exp, row sum, probability-weighted values; output into xs.  CH_SPLIT
+  // neighbouring lanes share a task, lane `part` with keys part, part + CH_SPLIT, ..
+  // (every lane of a wave runs the same number of rounds, so the exchanges see
+  // all of a task's lanes)
+  const int part = t % CH_SPLIT;
+  for (int t0 = 0; t0 < H * L * CH_SPLIT; t0 += CH_NT) {
+    const bool live = t0 + t < H * L * CH_SPLIT;
+    const int task = live ? (t0 + t) / CH_SPLIT : 0;
     const int h = task / L, i = task - h * L;
     float qr[D];
 #pragma unroll
@@ -158,13 +177,15 @@ __global__ __launch_bounds__(NTH) void chain_sublayer_f32_kernel(ChainParams p) 
     };
     float mx = -INFINITY;
 #pragma unroll 2
-    for (int j = 0; j < L; ++j) mx = fmaxf(mx, score(j));
+    for (int j = part; j < L; j += CH_SPLIT) mx = fmaxf(mx, score(j));
+#pragma unroll
+    for (int o = 1; o < CH_SPLIT; o *= 2) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
     float l = 0.0f;
     float o[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) o[d] = 0.0f;
 #pragma unroll 2
-    for (int j = 0; j < L; ++j) {
+    for (int j = part; j < L; j += CH_SPLIT) {
       const float e = expf(score(j) - mx);
       l += e;
       const float* vr = qs + j * QP + 2 * C + h * D;
@@ -177,11 +198,20 @@ __global__ __launch_bounds__(NTH) void chain_sublayer_f32_kernel(ChainParams p) 
         o[d + 3] = fmaf(e, v.w, o[d + 3]);
       }
     }
-    const float inv = 1.0f / l;
 #pragma unroll
-    for (int d = 0; d < D; d += 4)
-      *reinterpret_cast<float4*>(xs + i * C + h * D + d) =
-          make_float4(o[d] * inv, o[d + 1] * inv, o[d + 2] * inv, o[d + 3] * inv);
+    for (int x = 1; x < CH_SPLIT; x *= 2) {
+      l += __shfl_xor(l, x, 64);
+#pragma unroll
+      for (int d = 0; d < D; ++d) o[d] += __shfl_xor(o[d], x, 64);
+    }
+    const float inv = 1.0f / l;
+    if (live) {
+#pragma unroll
+      for (int d = 0; d < D; d += 4)
+        if ((d / 4) % CH_SPLIT == part)
+          *reinterpret_cast<float4*>(xs + i * WP + h * D + d) =
+              make_float4(o[d] * inv, o[d + 1] * inv, o[d + 2] * inv, o[d + 3] * inv);
+    }
   }
   __syncthreads();
 
@@ -189,13 +219,8 @@ __global__ __launch_bounds__(NTH) void chain_sublayer_f32_kernel(ChainParams p) 
   {
     const RowSwap rs = p.rs;
     float* const y = p.y;
-    const int bands = CH_NT / C;
-    const int n = t % C, band = t / C;
-    if (band < bands) {
-      const int rows = (L + bands - 1) / bands;
-      chain_gemm_col(xs, C, ws + n * WP, p.bo ? p.bo[n] : 0.0f, band * rows, min(L, (band + 1) * rows),
-                     [=](int m, float v) { y[rs.map((int)(row0 + m)) * C + n] = v; });
-    }
+    chain_gemm(xs, ws, WP, k16, p.bo, L, C, CH_NT / 64,
+               [=](int m, int n, float v) { y[rs.map((int)(row0 + m)) * C + n] = v; });
   }
 }
 
