@@ -33,6 +33,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "attn_bf16_common.h"
 #include "dsp_internal.h"
@@ -286,7 +287,7 @@ constexpr int staged_pitch(int elems) {
 //   dP^T = V dO^T - Delta (bias columns)     -> dZ^T = P^T * dP^T
 //   dQ^T += K^T dZ^T
 template <int D, int NW>
-__global__ __launch_bounds__(NW * 64, 2) void attn_bwd_dq_kernel(BwdParams p) {
+__global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 2) void attn_bwd_dq_kernel(BwdParams p) {
   using G = BGeo<D>;
   constexpr int KB = 64, NKT = KB / 32, NT = NW * 64, FT = NT / 2;
   constexpr int TCH = KB * G::CH;
@@ -389,53 +390,66 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bwd_dq_kernel(BwdParams p) {
     const bf16* k_lds = lds + (it & 1) * TILE;
     const bf16* v_lds = k_lds + KB * G::P;
 
-    floatx16 s[NKT], dp[NKT];
+    // key tiles LO .. HI - 1 of 32: scores, probabilities, their product with K
+    auto keys = [&](auto lo_c, auto hi_c) {
+      constexpr int LO = decltype(lo_c)::value, HI = decltype(hi_c)::value;
+      floatx16 s[NKT], dp[NKT];
 #pragma unroll
-    for (int kt = 0; kt < NKT; ++kt)
+      for (int kt = LO; kt < HI; ++kt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[kt][r] = dp[kt][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) s[kt][r] = dp[kt][r] = 0.0f;
 #pragma unroll
-    for (int st = 0; st < G::NDK; ++st)
+      for (int st = 0; st < G::NDK; ++st)
 #pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        const bf16x8 ka = *reinterpret_cast<const bf16x8*>(k_lds + (32 * kt + l32) * G::P + 16 * st + 8 * g);
-        const bf16x8 va = *reinterpret_cast<const bf16x8*>(v_lds + (32 * kt + l32) * G::P + 16 * st + 8 * g);
-        s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[st], s[kt], 0, 0, 0);
-        dp[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, df[st], dp[kt], 0, 0, 0);
+        for (int kt = LO; kt < HI; ++kt) {
+          const bf16x8 ka = *reinterpret_cast<const bf16x8*>(k_lds + (32 * kt + l32) * G::P + 16 * st + 8 * g);
+          const bf16x8 va = *reinterpret_cast<const bf16x8*>(v_lds + (32 * kt + l32) * G::P + 16 * st + 8 * g);
+          s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[st], s[kt], 0, 0, 0);
+          dp[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, df[st], dp[kt], 0, 0, 0);
+        }
+      // lane (n + 32g) holds keys kb + 32kt + 8(r/4) + 4g + r%4 of query n.
+      // Keys past Lk (only the last tile holds any) get score -inf, so P = +0
+      // there; the branch keeps the key compares out of every other tile.
+      if (kb + KB > Lk) {
+#pragma unroll
+        for (int kt = LO; kt < HI; ++kt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (kb + 32 * kt + (r / 4) * 8 + 4 * g + (r % 4) >= Lk) s[kt][r] = -INFINITY;
       }
-    // lane (n + 32g) holds keys kb + 32kt + 8(r/4) + 4g + r%4 of query n.
-    // Keys past Lk (only the last tile holds any) get score -inf, so P = +0
-    // there; the branch keeps the key compares out of every other tile.
-    if (kb + KB > Lk) {
+      bf16x8 zb[NKT][2];
 #pragma unroll
-      for (int kt = 0; kt < NKT; ++kt)
+      for (int kt = LO; kt < HI; ++kt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (kb + 32 * kt + (r / 4) * 8 + 4 * g + (r % 4) >= Lk) s[kt][r] = -INFINITY;
-    }
-    bf16x8 zb[NKT][2];
+        for (int r = 0; r < 16; ++r) zb[kt][r / 8][r % 8] = (bf16)(__builtin_amdgcn_exp2f(s[kt][r]) * dp[kt][r]);
+      // dQ^T += K^T dZ^T
 #pragma unroll
-    for (int kt = 0; kt < NKT; ++kt)
+      for (int t = 0; t < G::NT32; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) zb[kt][r / 8][r % 8] = (bf16)(__builtin_amdgcn_exp2f(s[kt][r]) * dp[kt][r]);
-    // dQ^T += K^T dZ^T
+        for (int kt = LO; kt < HI; ++kt)
 #pragma unroll
-    for (int t = 0; t < G::NT32; ++t)
+          for (int kk = 0; kk < 2; ++kk)
+            dqt[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                tr_frag32(k_lds, G::P, 32 * kt + 16 * kk, 32 * t, lane), zb[kt][kk], dqt[t], 0, 0, 0);
+      if constexpr (G::SLAB) {
 #pragma unroll
-      for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-          dqt[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              tr_frag32(k_lds, G::P, 32 * kt + 16 * kk, 32 * t, lane), zb[kt][kk], dqt[t], 0, 0, 0);
-    if constexpr (G::SLAB) {
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        const bf16x8 a = tr_slab(k_lds, G::P, 32 * kt, 32 * G::NT32, lane);
-        bf16x8 b0, b1;
-        slab_b(zb[kt][0], zb[kt][1], b0, b1);
-        dqs[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, dqs[0], 0, 0, 0);
-        dqs[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, dqs[1], 0, 0, 0);
+        for (int kt = LO; kt < HI; ++kt) {
+          const bf16x8 a = tr_slab(k_lds, G::P, 32 * kt, 32 * G::NT32, lane);
+          bf16x8 b0, b1;
+          slab_b(zb[kt][0], zb[kt][1], b0, b1);
+          dqs[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, dqs[0], 0, 0, 0);
+          dqs[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, dqs[1], 0, 0, 0);
+        }
       }
+    };
+    // 4 waves: one tile at a time, whose fewer live scores (168 registers) leave
+    // room for three work-groups on a CU instead of two
+    using std::integral_constant;
+    if constexpr (NW == 4) {
+      keys(integral_constant<int, 0>{}, integral_constant<int, 1>{});
+      keys(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    } else {
+      keys(integral_constant<int, 0>{}, integral_constant<int, NKT>{});
     }
     if (more) stash((it + 1) & 1);
     __syncthreads();
@@ -892,17 +906,19 @@ void fill_common(P& p, const AttnBwdArgs& a) {
   p.delta = a.delta;
 }
 
-// Waves (32 rows each) per work-group of the dQ and dK/dV kernels: 4 or 8, two
-// work-groups of 8 or three of 4 on a CU.  8 read the other side's tiles for twice the
-// rows; 4 leave fewer CUs idle where the launch is a few rounds or the rows end early
-// in a block.  `rows` owned rows per unit against `tiles` tiles of 64: full rounds of
-// 256 * levels work-groups and one of the rest, with 1 .. levels per CU, at a[j - 1] +
-// b[j - 1] * tiles microseconds a round, fitted to 71 shapes of self-attention (D = 72, 16
-// to 640 units, 150 to 3000 rows, both kernels together, relative error 5-7%).  Choosing
-// by it is within 0.3% of the better one on average and takes 9% off what 8 waves
-// need: 34 frames of 400 tokens (16 heads) 194 -> 165 us, 7 x 1350 290 -> 270, 16 units of
-// 1024 67 -> 54; 640 units of 1024 stay on 8.
-int bwd_waves(int64_t units, int64_t rows, int64_t tiles) {
+// Waves (32 rows each) per work-group of the dQ and dK/dV kernels: 4 or 8.  8 (one
+// work-group per CU, two where 256 registers a SIMD lane allow it) read the other
+// side's tiles for twice the rows; 4 leave fewer CUs idle where the launch is a few
+// rounds or the rows end early in a block.  `rows` owned rows per unit against `tiles`
+// tiles of 64: full rounds of 256 * levels work-groups and one of the rest, with
+// 1 .. levels per CU, at a[j - 1] + b[j - 1] * tiles microseconds a round, fitted to 71 shapes
+// of self-attention (D = 72, 16 to 640 units, 150 to 3000 rows, both kernels together,
+// relative error 5-7%).  Choosing by it is within 0.3% of the better one on average and
+// takes 9% off what 8 waves need: 34 frames of 400 tokens (16 heads) 194 -> 165 us, 7 x
+// 1350 290 -> 270, 16 units of 1024 67 -> 54.  `four`: what 4 waves cost against the fit;
+// dQ 0.94 since a CU holds three of its work-groups (32 x 1024 forward and backward 856
+// -> 826 us).
+int bwd_waves(int64_t units, int64_t rows, int64_t tiles, double four) {
   struct Shape {
     int waves, levels;
     double first, a[3], b[3];
@@ -919,7 +935,7 @@ int bwd_waves(int64_t units, int64_t rows, int64_t tiles) {
       cost[i] += q.a[j] + q.b[j] * (double)tiles;
     }
   }
-  return cost[1] < cost[0] ? 4 : 8;
+  return four * cost[1] < cost[0] ? 4 : 8;
 }
 
 template <int D, int NW>
@@ -1023,8 +1039,8 @@ int launch_bwd_d(const AttnBwdArgs& a, hipStream_t s) {
   if (L <= 64) return launch_bwd_two<D>(a, 2, 2, s);
   if (L <= 128) return launch_bwd_two<D>(a, 4, 4, s);
   const int64_t bx = a.B * a.X;
-  return launch_bwd_two<D>(a, bwd_waves(bx * a.H, a.L, (a.Lk + 63) / 64),
-                           bwd_waves(bx * a.Hkv, a.Lk, (a.H / a.Hkv) * ((a.L + 63) / 64)), s);
+  return launch_bwd_two<D>(a, bwd_waves(bx * a.H, a.L, (a.Lk + 63) / 64, 0.94),
+                           bwd_waves(bx * a.Hkv, a.Lk, (a.H / a.Hkv) * ((a.L + 63) / 64), 1.0), s);
 }
 
 }  // namespace
