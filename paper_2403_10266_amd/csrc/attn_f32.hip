@@ -526,7 +526,10 @@ int launch_units(Which which, ParamsF p, int64_t units, int64_t rows, hipStream_
   const int dp = padded_width(p.D);
   if (dp && blocks < (int64_t(1) << 31)) {
     const uint32_t n = (uint32_t)blocks;
-#define DSP_F32_CASE(DP_)                                                                          case DP_:                                                                                          nw == 1 ? launch_mfma<DP_, 1>(which, p, n, s) : launch_mfma<DP_, 4>(which, p, n, s);             break
+#define DSP_F32_CASE(DP_)                                                                            \
+  case DP_:                                                                                          \
+    nw == 1 ? launch_mfma<DP_, 1>(which, p, n, s) : launch_mfma<DP_, 4>(which, p, n, s);             \
+    break
     switch (dp) {
       DSP_F32_CASE(32);
       DSP_F32_CASE(64);

@@ -151,6 +151,8 @@ constexpr int DSP_EPI_GELU_KEEP_GRAD = 7, DSP_EPI_SCALE_BWD = 8;
 // Whether launch_linear_bf16 runs (M, N, K) on its pipelined or large tiles (not
 // on the 256 x 128 kernel it keeps for the other sizes).
 bool linear_bf16_tiled(int64_t M, int64_t N, int64_t K);
+// Whether (M, N) fills every CU with 256 x 256 (N < 2048: 256 x 192) tiles.
+bool linear_bf16_large_tiles(int64_t M, int64_t N);
 // y_i[c][r] = x_i[r][c] for n <= 6 bf16 matrices of rows_i x cols_i (multiples
 // of 8, 16-byte aligned), in one launch (gemm.hip).
 int launch_transpose_bf16_batch(const void* const* x, void* const* y, const int64_t* rows, const int64_t* cols,

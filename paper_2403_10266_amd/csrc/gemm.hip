@@ -1166,6 +1166,11 @@ int choose_tiles(int64_t M, int64_t N, int64_t K, bool act) {
   return best;
 }
 
+bool linear_bf16_large_tiles(int64_t M, int64_t N) {
+  return DSP_GEMM_BIG && N % 8 == 0 && (int64_t)BIG_BM * N * 4 < (int64_t(1) << 31) &&
+         tile_count(kTiles[N >= 2048 ? T_BIG256 : T_BIG192], M, N) >= 256;
+}
+
 // The tile shape a launch takes: 16-byte output chunks need N % 8 == 0, the
 // epilogue addresses a tile's rows of fp32 residual with 32-bit offsets, and the
 // pipelined tiles load whole K slices.  K not a multiple of 64: the register-
@@ -1174,8 +1179,7 @@ int choose_tiles(int64_t M, int64_t N, int64_t K, bool act) {
 int tile_shape(int64_t M, int64_t N, int64_t K, bool act) {
   if (!DSP_GEMM_BIG || N % 8 || (int64_t)BIG_BM * N * 4 >= (int64_t(1) << 31)) return -1;
   if (K % BK == 0) return choose_tiles(M, N, K, act);
-  const int big = N >= 2048 ? T_BIG256 : T_BIG192;
-  return tile_count(kTiles[big], M, N) >= 256 ? big : -1;
+  return linear_bf16_large_tiles(M, N) ? (N >= 2048 ? T_BIG256 : T_BIG192) : -1;
 }
 
 bool linear_bf16_tiled(int64_t M, int64_t N, int64_t K) { return tile_shape(M, N, K, false) >= 0; }
