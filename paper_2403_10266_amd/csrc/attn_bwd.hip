@@ -916,8 +916,8 @@ void fill_common(P& p, const AttnBwdArgs& a) {
 // relative error 5-7%).  Choosing by it is within 0.3% of the better one on average and
 // takes 9% off what 8 waves need: 34 frames of 400 tokens (16 heads) 194 -> 165 us, 7 x
 // 1350 290 -> 270, 16 units of 1024 67 -> 54.  `four`: what 4 waves cost against the fit;
-// dQ 0.94 since a CU holds three of its work-groups (32 x 1024 forward and backward 856
-// -> 826 us).
+// dQ 0.94 since a CU holds three of its work-groups (32 x 1024 forward and backward 857
+// -> 840 us).
 int bwd_waves(int64_t units, int64_t rows, int64_t tiles, double four) {
   struct Shape {
     int waves, levels;

@@ -699,7 +699,7 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_bf16_big_kernel(
 // 64-wide slice takes 0.23 us on 64 x 64 tiles, 0.50 on 64 x 128, 0.59 on 128 x 128,
 // 0.68 on 128 x 192 with a work-group per CU.  The schedule inside a slice, the MFMAs
 // and their k order are those of gemm_bf16_big_kernel: the same bits.
-//   1200 x 4608 x 1152 + GELU 48 -> 22 us, 300 x 1152 x 1152 + residual 38 -> 7.6,
+//   1200 x 4608 x 1152 + GELU 46 -> 21 us, 300 x 1152 x 1152 + residual 38 -> 7.6,
 // 2500 x 1152 x 4608 106 -> 51, 13600 x 1152 x 1152 65 -> 48 (256 x 128 or 256 x 192
 // tiles before).  Slices of 32 (256 x 128 and 128 x 256 tiles, two work-groups per
 // CU): 284 us against 239 for 128 x 192 tiles and 64-wide slices at 32768 x 3456 x 1152.
