@@ -718,6 +718,11 @@ __global__ __launch_bounds__(NW * 64, MINW) void attn_fwd_kernel(Params p) {
   }
 }
 
+// A work-group's query rows are addressed with 32-bit byte offsets.
+bool rows_fit(int64_t L, int queries, int64_t row_stride) {
+  return std::min<int64_t>(L, queries) * row_stride * 2 < (int64_t(1) << 31);
+}
+
 // Kernel parameters for a launch with QB queries per work-group and KB keys
 // per tile; returns the number of work-groups (0: nothing to do) or -1 when
 // the shape is out of range.
@@ -747,7 +752,7 @@ int64_t make_params(const AttnArgs& a, int QB, int KB, Params& p) {
   if (blocks == 0) return 0;
   // a tile's buffer resource addresses its rows with 32-bit byte offsets
   if (blocks >= (int64_t(1) << 31) || std::min<int64_t>(a.Lk, KB) * a.r_stride_kv * 2 >= (int64_t(1) << 31) ||
-      std::min<int64_t>(a.L, QB) * a.r_stride_in * 2 >= (int64_t(1) << 31))
+      !rows_fit(a.L, QB, a.r_stride_in))
     return -1;
   p.n_units = (uint32_t)units;
   p.n_qb = (uint32_t)n_qb;
@@ -809,15 +814,20 @@ int choose_queries(int64_t units, int64_t L, int64_t Lk) {
   return best;
 }
 
+// Queries per work-group for at most 32 keys: one wave and a 32-key tile suit few
+// queries (150: 13.0 against 15.0 us for 800 units), four waves on a half-empty
+// 64-key tile many (1024: 45 -> 33 us, 300: 5.4 -> 5.1 for 32 units).  Rows too far
+// apart for a block of 128 run in blocks of 32.
+int choose_queries_few_keys(int64_t L, int64_t row_stride) {
+  return L >= 256 && rows_fit(L, 128, row_stride) ? 128 : 32;
+}
+
 template <int D>
 int launch_d(const AttnArgs& a, hipStream_t s) {
   // few keys: all of a unit's keys are one tile, fetched at once (the tiling
-  // is chosen by the key count; any number of queries runs in query blocks).
-  // At most 32 keys: one wave and a 32-key tile suit few queries (150: 13.0
-  // against 15.0 us for 800 units), four waves on a half-empty 64-key tile many
-  // (1024: 45 -> 33 us, 300: 5.4 -> 5.1 for 32 units).
+  // is chosen by the key count; any number of queries runs in query blocks)
   if (a.Lk <= 32) {
-    if (a.L >= 256) return launch_cfg<D, 4, 1, 64, 3, 1>(a, s);
+    if (choose_queries_few_keys(a.L, a.r_stride_in) == 128) return launch_cfg<D, 4, 1, 64, 3, 1>(a, s);
     return launch_cfg<D, 1, 1, 32, 1, 1>(a, s);
   }
   if (a.Lk <= 64) return launch_cfg<D, 2, 1, 64, 2, 1>(a, s);
