@@ -794,13 +794,14 @@ constexpr int kMaxQueryBlock = 512;
 constexpr QueryBlock kSmallBlocks[2] = {{256, 2, {1.4, 4.8}, {1.38, 2.20}},
                                         {128, 3, {0.4, 2.2, 3.8}, {0.90, 1.35, 1.84}}};
 
-int choose_queries(int64_t units, int64_t L, int64_t Lk) {
+int choose_queries_many_keys(int64_t units, int64_t L, int64_t Lk) {
   const double tiles = (double)((Lk + 63) / 64);
   const int64_t rounds = (units * ((L + kMaxQueryBlock - 1) / kMaxQueryBlock) + 255) / 256;
   int best = kMaxQueryBlock;
   double best_cost = rounds == 1 ? 6.2 + 1.93 * tiles : (double)rounds * (7.1 + 2.09 * tiles);
   for (const QueryBlock& q : kSmallBlocks) {
     const int64_t blocks = units * ((L + q.queries - 1) / q.queries), round = 256 * q.levels, rest = blocks % round;
+    if (!grid_fits(blocks, 256)) continue;  // both have four waves: up to twice the threads of 512
     double cost = 3.9 + (double)(blocks / round) * (q.a[q.levels - 1] + q.b[q.levels - 1] * tiles);
     if (rest) {
       const int j = (int)((rest + 255) / 256) - 1;
@@ -817,17 +818,27 @@ int choose_queries(int64_t units, int64_t L, int64_t Lk) {
 // Queries per work-group for at most 32 keys: one wave and a 32-key tile suit few
 // queries (150: 13.0 against 15.0 us for 800 units), four waves on a half-empty
 // 64-key tile many (1024: 45 -> 33 us, 300: 5.4 -> 5.1 for 32 units).  Rows too far
-// apart for a block of 128 run in blocks of 32.
-int choose_queries_few_keys(int64_t L, int64_t row_stride) {
-  return L >= 256 && rows_fit(L, 128, row_stride) ? 128 : 32;
+// apart for a block of 128 run in blocks of 32, and so do units too many for a grid
+// of four-wave blocks (257 queries are 768 threads that way, 576 in blocks of 32).
+int choose_queries_few_keys(int64_t units, int64_t L, int64_t row_stride) {
+  return L >= 256 && rows_fit(L, 128, row_stride) && grid_fits(units * ((L + 127) / 128), 256) ? 128 : 32;
+}
+
+// Queries per work-group of a launch.
+int choose_queries(int64_t units, int64_t L, int64_t Lk, int64_t row_stride) {
+  if (Lk <= 32) return choose_queries_few_keys(units, L, row_stride);
+  if (Lk <= 64) return 64;
+  if (Lk <= 128) return DSP_TATTN_NW * DSP_TATTN_QT * 32;
+  return choose_queries_many_keys(units, L, Lk);
 }
 
 template <int D>
 int launch_d(const AttnArgs& a, hipStream_t s) {
   // few keys: all of a unit's keys are one tile, fetched at once (the tiling
   // is chosen by the key count; any number of queries runs in query blocks)
+  const int queries = choose_queries(a.B * a.X * a.H, a.L, a.Lk, a.r_stride_in);
   if (a.Lk <= 32) {
-    if (choose_queries_few_keys(a.L, a.r_stride_in) == 128) return launch_cfg<D, 4, 1, 64, 3, 1>(a, s);
+    if (queries == 128) return launch_cfg<D, 4, 1, 64, 3, 1>(a, s);
     return launch_cfg<D, 1, 1, 32, 1, 1>(a, s);
   }
   if (a.Lk <= 64) return launch_cfg<D, 2, 1, 64, 2, 1>(a, s);
@@ -838,7 +849,7 @@ int launch_d(const AttnArgs& a, hipStream_t s) {
       return launch_cfg<D, DSP_TATTN_NW, DSP_TATTN_QT, DSP_TATTN_KB, DSP_TATTN_MINW>(a, s);
   }
   static_assert(DSP_SATTN_NW * DSP_SATTN_QT * 32 == kMaxQueryBlock, "the largest query block");
-  switch (choose_queries(a.B * a.X * a.H, a.L, a.Lk)) {
+  switch (queries) {
     case 256: return launch_cfg<D, 4, 2, 64, 2>(a, s);
     case 128: return launch_cfg<D, 4, 1, 64, 3>(a, s);
     default: return launch_cfg<D, DSP_SATTN_NW, DSP_SATTN_QT, DSP_SATTN_KB, DSP_SATTN_MINW>(a, s);
@@ -846,6 +857,10 @@ int launch_d(const AttnArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+extern "C" int dsp_choice_attn_fwd(int D, int64_t units, int64_t L, int64_t Lk, int64_t q_row_stride) {
+  return attn_bf16_supports(D) ? choose_queries(units, L, Lk, q_row_stride) : 0;
+}
 
 bool attn_bf16_supports(int D) {
   switch (D) {

@@ -170,6 +170,14 @@ bool chain_sublayer_f32_fits(int64_t L, int C, int H);
 int launch_chain_sublayer_f32(const float* x, const float* wqkv, const float* bqkv, const float* wo, const float* bo,
                               float* y, int64_t groups, int L, int C, int H, float scale, RowSwap rs, hipStream_t s);
 
+// HIP launches fewer than 2^32 threads along a grid dimension.
+inline bool grid_fits(int64_t blocks, int threads) { return blocks * threads < (int64_t(1) << 32); }
+
+// Host-only queries of a launch's choice (no device is touched), for tests that
+// name the variant they mean to run.
+//   Queries per work-group of the bf16 attention forward.
+extern "C" int dsp_choice_attn_fwd(int D, int64_t units, int64_t L, int64_t Lk, int64_t q_row_stride);
+
 inline int hip_status(hipError_t e) { return e == hipSuccess ? DSP_OK : DSP_ERR_HIP; }
 inline int last_launch_status() { return hip_status(hipGetLastError()); }
 

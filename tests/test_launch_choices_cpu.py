@@ -1,0 +1,32 @@
+"""The variants that launches choose, asked without a device: a choice has to be one
+that can be launched wherever another variant can (a grid dimension takes fewer than
+2^32 threads), and the variants that the GPU tests name are the ones they run."""
+import ctypes
+
+import pytest
+
+import paper_2403_10266_amd as dsp
+
+I64, INT = ctypes.c_int64, ctypes.c_int
+GRID_THREADS = 1 << 32
+
+
+def attn_fwd(D, units, L, Lk, stride=1152):
+    f = dsp.lib().dsp_choice_attn_fwd
+    f.restype, f.argtypes = INT, [INT, I64, I64, I64, I64]
+    return f(D, units, L, Lk, stride)
+
+
+# threads of a work-group by its queries, for more than 128 keys and for at most 32
+ATTN_THREADS = {"many": {512: 512, 256: 256, 128: 256}, "few": {128: 256, 32: 64}}
+
+
+@pytest.mark.parametrize("L", [256, 257, 300, 512, 1000, 4096])
+@pytest.mark.parametrize("Lk", [1, 20, 32, 129, 300, 1000])
+def test_attention_forward_grid(L, Lk):
+    kind = "few" if Lk <= 32 else "many"
+    threads, base = ATTN_THREADS[kind], 32 if Lk <= 32 else 512
+    most = (GRID_THREADS - 1) // (-(-L // base) * threads[base])    # units that blocks of `base` queries can launch
+    for units in (most, most - 1, most * 3 // 4, most // 2 + 1, most // 2):
+        q = attn_fwd(16, units, L, Lk)
+        assert units * -(-L // q) * threads[q] < GRID_THREADS, (units, q)
