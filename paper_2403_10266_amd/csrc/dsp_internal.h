@@ -177,6 +177,9 @@ inline bool grid_fits(int64_t blocks, int threads) { return blocks * threads < (
 // name the variant they mean to run.
 //   Queries per work-group of the bf16 attention forward.
 extern "C" int dsp_choice_attn_fwd(int D, int64_t units, int64_t L, int64_t Lk, int64_t q_row_stride);
+//   Output tile of the bf16 GEMM, rows << 16 | columns (| 1 << 31: four K slices in
+// flight where two are usual), for the plain GELU epilogue or another.
+extern "C" uint32_t dsp_choice_linear(int64_t M, int64_t N, int64_t K, int gelu);
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? DSP_OK : DSP_ERR_HIP; }
 inline int last_launch_status() { return hip_status(hipGetLastError()); }

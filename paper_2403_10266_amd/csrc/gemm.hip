@@ -1151,6 +1151,7 @@ int choose_tiles(int64_t M, int64_t N, int64_t K, bool act) {
     const TileShape& t = kTiles[i];
     const int64_t tiles = tile_count(t, M, N), round = 256 * t.levels;
     if (i <= T_BIG192 && (tiles < 256 || (i == T_BIG256) != (N >= 2048))) continue;
+    if (!grid_fits(tiles, NTHR)) continue;  // 2^30 rows and more: the taller tiles
     const int64_t rest = tiles % round;
     const double extra = act ? t.act : 0.0;
     double cost = (double)(tiles / round) * (t.a[t.levels - 1] + t.b[t.levels - 1] * slices + extra);
@@ -1183,6 +1184,12 @@ int tile_shape(int64_t M, int64_t N, int64_t K, bool act) {
 }
 
 bool linear_bf16_tiled(int64_t M, int64_t N, int64_t K) { return tile_shape(M, N, K, false) >= 0; }
+
+extern "C" uint32_t dsp_choice_linear(int64_t M, int64_t N, int64_t K, int gelu) {
+  const int i = tile_shape(M, N, K, gelu != 0);
+  if (i < 0) return (uint32_t)(BM << 16 | BN);
+  return (uint32_t)(kTiles[i].bm << 16 | kTiles[i].bn) | (i == T_128x128_DEEP ? 1u << 31 : 0u);
+}
 
 int launch_linear_bf16(const void* a, const void* w, const void* bias, const float* residual,
                        void* out, int64_t M, int N, int K, int epilogue, hipStream_t s, void* pre, RowSwap rs) {

@@ -30,3 +30,22 @@ def test_attention_forward_grid(L, Lk):
     for units in (most, most - 1, most * 3 // 4, most // 2 + 1, most // 2):
         q = attn_fwd(16, units, L, Lk)
         assert units * -(-L // q) * threads[q] < GRID_THREADS, (units, q)
+
+
+def linear(M, N, K, gelu=False):
+    """(rows, columns, whether four K slices are in flight) of the output tile"""
+    f = dsp.lib().dsp_choice_linear
+    f.restype, f.argtypes = ctypes.c_uint32, [I64, I64, I64, INT]
+    v = f(M, N, K, gelu)
+    return (v >> 16) & 0x7FFF, v & 0xFFFF, bool(v >> 31)
+
+
+@pytest.mark.parametrize("N", [8, 64, 136, 1152])
+@pytest.mark.parametrize("K", [64, 1024])
+def test_linear_grid(N, K):
+    # launches that 256-row tiles (256 threads) can make
+    most = (GRID_THREADS // 256 - 1) // -(-N // 192) * 256
+    for M in (1 << 20, 1 << 24, 1 << 28, (1 << 30) - 64, 1 << 30, (1 << 30) + 64, 3 << 29, (1 << 31) - 256):
+        if M <= most:
+            rows, cols, _ = linear(M, N, K)
+            assert -(-M // rows) * -(-N // cols) * 256 < GRID_THREADS, (M, rows, cols)
