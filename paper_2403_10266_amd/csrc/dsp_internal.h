@@ -172,6 +172,8 @@ int launch_chain_sublayer_f32(const float* x, const float* wqkv, const float* bq
 
 // HIP launches fewer than 2^32 threads along a grid dimension.
 inline bool grid_fits(int64_t blocks, int threads) { return blocks * threads < (int64_t(1) << 32); }
+// The most work-groups of one launch, a multiple of 8 (whole XCD rounds).
+inline int64_t grid_blocks(int threads) { return ((int64_t(1) << 32) / threads - 1) & ~int64_t(7); }
 
 // Host-only queries of a launch's choice (no device is touched), for tests that
 // name the variant they mean to run.

@@ -33,6 +33,8 @@
 // where the rows allow them, single floats otherwise (a wave-uniform choice).
 #include <math.h>
 
+#include <algorithm>
+
 #include "dsp_internal.h"
 
 namespace dsp {
@@ -55,6 +57,7 @@ struct F32Gemm {
   float* pre;          // FE_GELU / FE_RELU: also receives the pre-activation (may be null)
   int64_t lda, ldb, M, N, K;
   uint32_t n_mt, n_nt;
+  uint32_t first, count;  // this launch's tiles
   int epi;
   bool vec_n;  // 16-byte stores allowed
   RowSwap rs;
@@ -165,9 +168,9 @@ __global__ __launch_bounds__(FTHR* KS) void gemm_f32_mfma_kernel(F32Gemm p) {
 
   // Tile order: a contiguous range of tiles per XCD (one L2 each), in groups of
   // 8 m-tiles with m fastest, so the tiles running together share A and B rows.
-  const uint32_t n_tiles = p.n_mt * p.n_nt, per = n_tiles >> 3, extra = n_tiles & 7u;
+  const uint32_t per = p.count >> 3, extra = p.count & 7u;
   const uint32_t xcd = blockIdx.x & 7u;
-  const uint32_t tile = xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
+  const uint32_t tile = p.first + xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
   const uint32_t grp = tile / (8 * p.n_nt), first = grp * 8;
   const uint32_t gm = p.n_mt - first < 8 ? p.n_mt - first : 8, rem = tile - grp * 8 * p.n_nt;
   const int64_t m0 = (int64_t)(first + rem % gm) * FT, n0 = (int64_t)(rem / gm) * FT;
@@ -295,7 +298,6 @@ int launch_f32(F32Gemm p, hipStream_t s) {
   p.n_mt = (uint32_t)n_mt;
   p.n_nt = (uint32_t)n_nt;
   const int64_t tiles = n_mt * n_nt;
-  const dim3 grid((uint32_t)tiles);
   const int ks = tiles <= 256 && p.K >= 16 * FBK ? 4 : tiles <= 512 && p.K >= 8 * FBK ? 2 : 1;
   const dim3 block((uint32_t)(ks * FTHR));
 #define DSP_F32_LAUNCH(KS_)                                                               \
@@ -305,14 +307,23 @@ int launch_f32(F32Gemm p, hipStream_t s) {
     else                                                                                  \
       hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, KS_, false>), grid, block, 0, s, p); \
   } while (0)
-  if (ks == 4)
-    DSP_F32_LAUNCH(4);
-  else if (ks == 2)
-    DSP_F32_LAUNCH(2);
-  else
-    DSP_F32_LAUNCH(1);
+  // one launch, or several where the threads are too many for a grid (2^30 rows)
+  const int64_t most = grid_blocks(ks * FTHR);
+  for (int64_t first = 0; first < tiles; first += most) {
+    p.first = (uint32_t)first;
+    p.count = (uint32_t)std::min(most, tiles - first);
+    const dim3 grid(p.count);
+    if (ks == 4)
+      DSP_F32_LAUNCH(4);
+    else if (ks == 2)
+      DSP_F32_LAUNCH(2);
+    else
+      DSP_F32_LAUNCH(1);
+    const int st = last_launch_status();
+    if (st != DSP_OK) return st;
+  }
 #undef DSP_F32_LAUNCH
-  return last_launch_status();
+  return DSP_OK;
 }
 
 }  // namespace
