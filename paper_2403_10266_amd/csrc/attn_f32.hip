@@ -28,6 +28,8 @@
 // 32-column slice of the output), plain FMAs.
 #include <math.h>
 
+#include <algorithm>
+
 #include "dsp_internal.h"
 
 namespace dsp {
@@ -54,6 +56,7 @@ struct ParamsF {
   int64_t b_q, x_q, r_q, b_kv, x_kv, r_kv, b_o, x_o, r_o;
   int64_t X, H, L, Lk, grp, D, n_dc;
   int64_t n_blk;  // row blocks per unit
+  int64_t first;  // this launch's first block
   float scale;
   bool vec;       // every row starts on 16 bytes and D is a multiple of 4
 };
@@ -161,9 +164,9 @@ __device__ __forceinline__ void store_own(float* row, const floatx16 (&acc)[NT],
 
 // The work-group's block of a unit's rows: units in contiguous ranges per XCD
 // (their tiles are then shared through one L2).
-__device__ __forceinline__ uint32_t xcd_block() {
+__device__ __forceinline__ int64_t xcd_block(int64_t first) {
   const uint32_t n = gridDim.x, per = n >> 3, extra = n & 7u, xcd = blockIdx.x & 7u;
-  return xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
+  return first + (xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3));
 }
 
 template <int DP, int NW>
@@ -178,7 +181,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_mfma_kernel(ParamsF p) {
   constexpr int NB = G::NB, NT = G::NT, TE = G::Tile::ELEMS;
   __shared__ __attribute__((aligned(16))) float lds[NB * 2 * TE];
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
-  const uint32_t blk = xcd_block();
+  const int64_t blk = xcd_block(p.first);
   const int64_t unit = blk / p.n_blk, qi = (blk % p.n_blk) * (32 * NW) + 32 * (threadIdx.x >> 6) + l32;
   const int64_t h = unit % p.H, bx = unit / p.H, xx = bx % p.X, bb = bx / p.X;
   const bool valid = qi < p.L;
@@ -249,7 +252,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dq_mfma_kernel(ParamsF p
   constexpr int NB = G::NB, NT = G::NT, TE = G::Tile::ELEMS;
   __shared__ __attribute__((aligned(16))) float lds[NB * 2 * TE];
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
-  const uint32_t blk = xcd_block();
+  const int64_t blk = xcd_block(p.first);
   const int64_t unit = blk / p.n_blk, qi = (blk % p.n_blk) * (32 * NW) + 32 * (threadIdx.x >> 6) + l32;
   const int64_t h = unit % p.H, bx = unit / p.H, xx = bx % p.X, bb = bx / p.X;
   const bool valid = qi < p.L;
@@ -316,7 +319,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dkv_mfma_kernel(ParamsF 
   constexpr int NB = G::NB, NT = G::NT, TE = G::Tile::ELEMS;
   __shared__ __attribute__((aligned(16))) float lds[NB * (2 * TE + 64)];
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
-  const uint32_t blk = xcd_block();
+  const int64_t blk = xcd_block(p.first);
   const int64_t Hkv = p.H / p.grp;
   const int64_t unit = blk / p.n_blk, key = (blk % p.n_blk) * (32 * NW) + 32 * (threadIdx.x >> 6) + l32;
   const int64_t hk = unit % Hkv, bx = unit / Hkv, xx = bx % p.X, bb = bx / p.X;
@@ -524,21 +527,27 @@ int launch_units(Which which, ParamsF p, int64_t units, int64_t rows, hipStream_
   p.n_blk = (rows + 32 * nw - 1) / (32 * nw);
   const int64_t blocks = units * p.n_blk;
   const int dp = padded_width(p.D);
-  if (dp && blocks < (int64_t(1) << 31)) {
-    const uint32_t n = (uint32_t)blocks;
+  if (dp) {
+    // one launch, or several where the threads are too many for a grid
+    const int64_t most = grid_blocks(64 * nw);
+    for (p.first = 0; p.first < blocks; p.first += most) {
+      const uint32_t n = (uint32_t)std::min(most, blocks - p.first);
 #define DSP_F32_CASE(DP_)                                                                            \
   case DP_:                                                                                          \
     nw == 1 ? launch_mfma<DP_, 1>(which, p, n, s) : launch_mfma<DP_, 4>(which, p, n, s);             \
     break
-    switch (dp) {
-      DSP_F32_CASE(32);
-      DSP_F32_CASE(64);
-      DSP_F32_CASE(72);
-      DSP_F32_CASE(96);
-      default: nw == 1 ? launch_mfma<128, 1>(which, p, n, s) : launch_mfma<128, 4>(which, p, n, s);
-    }
+      switch (dp) {
+        DSP_F32_CASE(32);
+        DSP_F32_CASE(64);
+        DSP_F32_CASE(72);
+        DSP_F32_CASE(96);
+        default: nw == 1 ? launch_mfma<128, 1>(which, p, n, s) : launch_mfma<128, 4>(which, p, n, s);
+      }
 #undef DSP_F32_CASE
-    return last_launch_status();
+      const int st = last_launch_status();
+      if (st != DSP_OK) return st;
+    }
+    return DSP_OK;
   }
   const int64_t total = units * rows * p.n_dc, gen = (total + 255) / 256;
   if (gen >= (int64_t(1) << 31)) return DSP_ERR_SHAPE;

@@ -45,3 +45,22 @@ def test_linear_bwd_f32(torch):
     _product(torch, dsp.dsp_linear_bwd_data(x.view(n, 1), torch.full((1, 1), 5.0, device="cuda:0")), x, 5.0)
     dw, _ = dsp.dsp_linear_bwd_weight(torch.full((1, 1), 7.0, device="cuda:0"), x.view(1, n))
     _product(torch, dw, x, 7.0)
+
+
+def test_attention_f32_units(torch):
+    """2^24 and some units of 33 rows, head width 1: forward and gradients of the units
+    on both sides of the first grid's end, and of the last ones, against a run of theirs."""
+    import paper_2403_10266_amd as dsp
+    X, L = (1 << 24) + 40, 33
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+    q, k, v, do = (torch.randn((1, X, L, 1), generator=gen, device="cuda:0") for _ in range(4))
+    say(f"attention fp32 X={X} L={L} D=1")
+    o, lse = dsp.dsp_attn_general(q, k, v, 1, 1, with_lse=True)
+    grads = dsp.dsp_attn_general_bwd(q, k, v, o, do, lse, 1, 1)
+    for x in (0, X // 2 - 100, X - 200):
+        at = slice(x, x + 200)
+        qs, ks, vs, ds = (t[0, at].clone()[None] for t in (q, k, v, do))
+        want, wl = dsp.dsp_attn_general(qs, ks, vs, 1, 1, with_lse=True)
+        wg = dsp.dsp_attn_general_bwd(qs, ks, vs, want, ds, wl, 1, 1)
+        for got, w in ((o, want), (lse, wl), *zip(grads, wg)):
+            assert torch.equal(got[:, at], w), x
