@@ -289,7 +289,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float4* __rest
 constexpr int CS_THREADS = 1024, CS_UNROLL = 8;
 
 template <bool BF, int G>
-__global__ __launch_bounds__(CS_THREADS) void colsum_kernel(const void* __restrict__ dyp, float* db, int64_t M, int N) {
+__global__ __launch_bounds__(CS_THREADS) void colsum_kernel(const void* __restrict__ dyp, float* db, int64_t M, int N,
+                                                            int first) {  // this launch's first work-group
   constexpr int V = BF ? 8 : 1;              // columns per thread
   constexpr int R = CS_THREADS / G;          // rows per step
   constexpr int W = CS_THREADS / 64;
@@ -298,6 +299,7 @@ __global__ __launch_bounds__(CS_THREADS) void colsum_kernel(const void* __restri
   const uint32_t nb = gridDim.x;
   uint32_t bid = blockIdx.x;
   if ((nb & 7u) == 0) bid = (bid & 7u) * (nb >> 3) + (bid >> 3);
+  bid += (uint32_t)first;
   const int c = threadIdx.x % G, r = threadIdx.x / G;
   const int n = ((int)bid * G + c) * V;
   float s[V];
@@ -646,9 +648,15 @@ int launch_add_f32(const float* a, const float* b, float* out, int64_t n, hipStr
 int launch_colsum_f32(const float* dy, float* db, int64_t M, int N, hipStream_t s) {
   if (N == 0) return DSP_OK;
   constexpr int G = 16;
-  hipLaunchKernelGGL((colsum_kernel<false, G>), dim3((uint32_t)((N + G - 1) / G)), dim3(CS_THREADS), 0, s, dy, db, M,
-                     N);
-  return last_launch_status();
+  // one launch, or several where the threads are too many for a grid (2^26 columns)
+  const int64_t groups = ((int64_t)N + G - 1) / G, most = grid_blocks(CS_THREADS);
+  for (int64_t first = 0; first < groups; first += most) {
+    hipLaunchKernelGGL((colsum_kernel<false, G>), dim3((uint32_t)std::min(most, groups - first)), dim3(CS_THREADS), 0,
+                       s, dy, db, M, N, (int)first);
+    const int st = last_launch_status();
+    if (st != DSP_OK) return st;
+  }
+  return DSP_OK;
 }
 
 // The partials a caller's workspace provides for (the launch takes as many as it
@@ -715,9 +723,11 @@ int launch_gemm_grad(const void* a, int ta, int64_t lda, const void* b, int tb, 
 int launch_colsum_bf16(const void* dy, float* db, int64_t M, int N, hipStream_t s) {
   if (N == 0) return DSP_OK;
   if (N >= 128 * 32)
-    hipLaunchKernelGGL((colsum_kernel<true, 4>), dim3((uint32_t)((N + 31) / 32)), dim3(CS_THREADS), 0, s, dy, db, M, N);
+    hipLaunchKernelGGL((colsum_kernel<true, 4>), dim3((uint32_t)((N + 31) / 32)), dim3(CS_THREADS), 0, s, dy, db, M, N,
+                       0);
   else
-    hipLaunchKernelGGL((colsum_kernel<true, 2>), dim3((uint32_t)((N + 15) / 16)), dim3(CS_THREADS), 0, s, dy, db, M, N);
+    hipLaunchKernelGGL((colsum_kernel<true, 2>), dim3((uint32_t)((N + 15) / 16)), dim3(CS_THREADS), 0, s, dy, db, M, N,
+                       0);
   return last_launch_status();
 }
 

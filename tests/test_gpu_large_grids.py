@@ -64,3 +64,12 @@ def test_attention_f32_units(torch):
         wg = dsp.dsp_attn_general_bwd(qs, ks, vs, want, ds, wl, 1, 1)
         for got, w in ((o, want), (lse, wl), *zip(grads, wg)):
             assert torch.equal(got[:, at], w), x
+
+
+def test_bias_gradient_f32_columns(torch):
+    import paper_2403_10266_amd as dsp
+    n = (1 << 27) + 17
+    dy = _ramp(torch, n)
+    say(f"bias gradient fp32 of {n} columns")
+    _, db = dsp.dsp_linear_bwd_weight(dy.view(1, n), torch.full((1, 1), 2.0, device="cuda:0"), with_bias=True)
+    _product(torch, db, dy, 1.0)
