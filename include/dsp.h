@@ -343,7 +343,7 @@ int dsp_layernorm_bwd(const void* x, int x_dtype, const void* dy, int dy_dtype, 
  *
  * a:        [M, K] of dtype.
  * w:        [N, K] of dtype (stored [out][in]).
- * bias:     [N] of dtype, or NULL.
+ * bias:     [N] of dtype at any element's address (4-byte aligned is fastest), or NULL.
  * residual: [M, N] fp32 or NULL; required iff DSP_EPI_RESID.  May equal out.
  * out:      [M, N]; dtype for DSP_EPI_NONE / DSP_EPI_GELU / DSP_EPI_RELU,
  *           fp32 for DSP_EPI_F32 (out = a*W + bias) and DSP_EPI_RESID

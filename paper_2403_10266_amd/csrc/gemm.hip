@@ -1176,10 +1176,10 @@ bool linear_bf16_large_tiles(int64_t M, int64_t N) {
 // epilogue addresses a tile's rows of fp32 residual with 32-bit offsets, and the
 // pipelined tiles load whole K slices.  K not a multiple of 64: the register-
 // staged large tiles, which mask the tail, where they fill every CU; -1: the
-// 256 x 128 kernel, which takes anything.
-int tile_shape(int64_t M, int64_t N, int64_t K, bool act) {
+// 256 x 128 kernel, which takes anything.  big_only: no pipelined tiles.
+int tile_shape(int64_t M, int64_t N, int64_t K, bool act, bool big_only = false) {
   if (!DSP_GEMM_BIG || N % 8 || (int64_t)BIG_BM * N * 4 >= (int64_t(1) << 31)) return -1;
-  if (K % BK == 0) return choose_tiles(M, N, K, act);
+  if (K % BK == 0 && !big_only) return choose_tiles(M, N, K, act);
   return linear_bf16_large_tiles(M, N) ? (N >= 2048 ? T_BIG256 : T_BIG192) : -1;
 }
 
@@ -1210,7 +1210,13 @@ int launch_linear_bf16(const void* a, const void* w, const void* bias, const flo
   const bf16* Wt = static_cast<const bf16*>(w);
   const bf16* bs = static_cast<const bf16*>(bias);
   bf16* pb = static_cast<bf16*>(pre);
-  const int shape = tile_shape(M, N, K, epilogue == DSP_EPI_GELU && !keep);
+  // The tiles read the bias 8 bytes at a time.  A bias that starts off 4 bytes (a slice
+  // of a packed buffer) keeps to the 256 x 128 kernel, which reads single elements,
+  // where a launch does not fill every CU with large tiles; those take any address
+  // (unaligned buffer loads are on for every HSA process).  A branch between the two
+  // ways to load in the tiles themselves cost every launch 2% (K = 64: up to 8%).
+  const bool off4 = reinterpret_cast<uintptr_t>(bias) % 4 != 0;
+  const int shape = tile_shape(M, N, K, epilogue == DSP_EPI_GELU && !keep, off4);
   const int64_t st_tiles = shape < 0 ? tiles : tile_count(kTiles[shape], M, N);
   const int64_t st_nt = shape < 0 ? n_nt : (N + kTiles[shape].bn - 1) / kTiles[shape].bn;
   if (st_tiles >= (int64_t(1) << 31)) return DSP_ERR_SHAPE;

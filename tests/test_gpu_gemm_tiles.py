@@ -63,3 +63,19 @@ def test_block_train_small_tiles(torch, flags, T, S):
     derivative, its use in the backward) on 64-row tiles."""
     w = synth.Workload("block_64", "block", "bf16", B=2, T=T, S=S, C=128, H=2, F=256, seed=31)
     _train_case(torch, w, True, flags)
+
+
+@pytest.mark.parametrize("offset", [1, 2, 3])
+@pytest.mark.parametrize("M,N,K", [(65, 200, 448), (130, 1160, 320), (2001, 1160, 4608), (4501, 3464, 1152),
+                                   (8001, 4616, 1152), (14000, 1160, 4608), (100, 100, 72)])
+def test_bias_alignment(torch, M, N, K, offset):
+    """A bias that starts `offset` elements into a buffer: the bits of an aligned one."""
+    import paper_2403_10266_amd as dsp
+    gen = torch.Generator(device="cuda:0").manual_seed(M + offset)
+    a, w, buf = (torch.randn(s, generator=gen, device="cuda:0").to(torch.bfloat16) for s in ((M, K), (N, K), (N + 4,)))
+    b = buf[offset:offset + N]
+    r = torch.randn((M, N), generator=gen, device="cuda:0")
+    say(f"gemm bias offset={offset} M={M} N={N} K={K}")
+    assert b.data_ptr() % 8 == 2 * offset
+    for code, resid in ((dsp.DSP_EPI_NONE, None), (dsp.DSP_EPI_GELU, None), (dsp.DSP_EPI_RESID, r)):
+        assert torch.equal(dsp.dsp_linear(a, w, b, resid, code), dsp.dsp_linear(a, w, b.clone(), resid, code)), code
