@@ -222,7 +222,8 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_mfma_kernel(ParamsF p) {
     }
     mt = fmaxf(mt, other_half(mt));
     if (__any(mt > m)) {
-      const float mn = fmaxf(m, mt), corr = expf(m - mn);  // 0 for the first tile
+      // corr is 0 for the first tile, and 1 for a row whose scores are all -inf so far
+      const float mn = fmaxf(m, mt), corr = m == mn ? 1.0f : expf(m - mn);
       l *= corr;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
@@ -231,15 +232,17 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_mfma_kernel(ParamsF p) {
       m = mn;
     }
     float sum = 0.0f;
+    const float ref = m == -INFINITY ? 0.0f : m;  // no finite score yet: probabilities 0, not NaN
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[0][r] = expf(s[0][r] - m);
+      s[0][r] = expf(s[0][r] - ref);
       sum += s[0][r];
     }
     l += sum;
     drow_product<DP, NT>(vs, s[0], p.Lk - k0, l32, g, o);
   }
   l += other_half(l);
+  if (m == -INFINITY) l = NAN;  // a softmax over scores that are all -inf
   if (!valid) return;
   store_own<NT>(p.out_o + bb * p.b_o + xx * p.x_o + h * p.D + qi * p.r_o, o, p.D, p.vec, g, 1.0f / l);
   if (p.out_lse && g == 0) p.out_lse[unit * p.L + qi] = m + logf(l);
