@@ -305,9 +305,9 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dq_mfma_kernel(ParamsF p
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      float pr = expf(s[0][r] * p.scale - lse);
-      if (k0 + 32 > p.Lk && k0 + 8 * (r / 4) + 4 * g + r % 4 >= p.Lk) pr = 0.0f;
-      s[0][r] = pr * (s[1][r] - delta);
+      s[0][r] = expf(s[0][r] * p.scale - lse) * (s[1][r] - delta);
+      // (the whole product: an infinite Delta or dO row times 0 is not 0)
+      if (k0 + 32 > p.Lk && k0 + 8 * (r / 4) + 4 * g + r % 4 >= p.Lk) s[0][r] = 0.0f;
     }
     drow_product<DP, NT>(ks, s[0], p.Lk - k0, l32, g, dq);
   }
@@ -344,7 +344,6 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dkv_mfma_kernel(ParamsF 
     dt.load(p.dout + bb * p.b_o + xx * p.x_o + hq * p.D + r0 * p.r_o, p.r_o, p.L - r0, p.D, p.vec);
     if (threadIdx.x < 64) {
       const int64_t r = r0 + l32, at = (bx * p.H + hq) * p.L + r;
-      // rows past L: lse +inf, so their probabilities are 0
       stat = threadIdx.x < 32 ? (r < p.L ? p.lse[at] : INFINITY) : (r < p.L ? p.delta[at] : 0.0f);
     }
   };
@@ -361,6 +360,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dkv_mfma_kernel(ParamsF 
     __syncthreads();
     if (i + 1 < n) fetch(i + 1);
     if (NB == 2) buf ^= 1;
+    const int64_t left = p.L - (i % n_q) * 32;
     floatx16 s[2];
     zero(s);
 #pragma unroll
@@ -378,9 +378,10 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dkv_mfma_kernel(ParamsF 
         const int r = 4 * r4 + e;
         s[0][r] = expf(s[0][r] * p.scale - lv[e]);
         s[1][r] = s[0][r] * (s[1][r] - dl[e]);
+        // rows past L hold zeros, which an infinite key or value makes NaN
+        if (left < 32 && 8 * r4 + 4 * g + e >= left) s[0][r] = s[1][r] = 0.0f;
       }
     }
-    const int64_t left = p.L - (i % n_q) * 32;
     drow_product<DP, NT>(ds, s[0], left, l32, g, dv);
     drow_product<DP, NT>(qs, s[1], left, l32, g, dk);
   }

@@ -51,3 +51,37 @@ def test_masked_keys(L, Lk, D, masked):
         _same(lse[0, 0, 0], wl, "lse")
     else:
         assert bool(torch.isnan(lse).all())
+
+
+def _grads(q, k, v, o, do, lse):
+    """The gradients of the general definition, row by row: P = exp(S - lse)."""
+    q, k, v, o, do = (t[0, 0].double() for t in (q, k, v, o, do))
+    scale = q.shape[-1] ** -0.5
+    p = (q @ k.t() * scale - lse[0, 0, 0].double()[:, None]).exp()
+    dz = p * (do @ v.t() - (do * o).sum(-1, keepdim=True))
+    return dz @ k * scale, dz.t() @ q * scale, p.t() @ do
+
+
+@pytest.mark.parametrize("L,Lk,D", [(30, 33, 40), (5, 20, 72), (35, 130, 128), (130, 35, 16)])
+@pytest.mark.parametrize("what", ["key", "dout"])
+def test_gradients_with_an_infinite_row(L, Lk, D, what):
+    """A key of -inf (probability 0 under positive queries), or an infinite gradient row:
+    the rows and keys that fill a tile up add nothing to the others' gradients."""
+    import torch
+
+    import paper_2403_10266_amd as dsp
+    q, k, v, do = _case(L, Lk, D, L + Lk + D)
+    v = v.abs() + 0.1
+    if what == "key":
+        k[0, 0, 3] = -INF
+    o, lse = dsp.dsp_attn_general(q.cuda(), k.cuda(), v.cuda(), 1, 1, with_lse=True)
+    if what == "dout":
+        k = k.abs() + 0.1          # dQ = dZ K: one sign for the infinite row
+        o, lse = dsp.dsp_attn_general(q.cuda(), k.cuda(), v.cuda(), 1, 1, with_lse=True)
+        do[0, 0, 2] = INF
+        o[0, 0, 2] = -1.0          # Delta of that row is -inf, so dZ is +inf there
+    say(f"infinite {what} L={L} Lk={Lk} D={D}")
+    got = dsp.dsp_attn_general_bwd(q.cuda(), k.cuda(), v.cuda(), o, do.cuda(), lse, 1, 1)
+    want = _grads(q, k, v, o.cpu(), do, lse.cpu())
+    for g, w, name in zip(got, want, ("dq", "dk", "dv")):
+        _same(g[0, 0], w, name)
