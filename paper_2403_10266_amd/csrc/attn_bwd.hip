@@ -286,8 +286,15 @@ constexpr int staged_pitch(int elems) {
 //   S^T = K Q'^T - lse2   (bias columns)     -> P^T = exp2(S^T)
 //   dP^T = V dO^T - Delta (bias columns)     -> dZ^T = P^T * dP^T
 //   dQ^T += K^T dZ^T
-template <int D, int NW>
-__global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 2) void attn_bwd_dq_kernel(BwdParams p) {
+// Four-wave dQ work-groups take one 32-key tile at a time where that lets three of them
+// share a CU: at most 168 registers, and 3 x 2 tiles of 64 keys of K and V within 160 KB
+// of LDS.  Wider heads (80: 184 KB) hold two whatever the registers, and two tiles'
+// scores at once are then faster (80, 16 heads of 150 and 1024 keys: 54 and 2905 us the
+// gradients, 57 and 3010 one tile at a time).
+constexpr bool dq_one_tile(int D) { return D <= 72; }
+
+template <int D, int NW, bool ONE>
+__global__ __launch_bounds__(NW * 64, ONE ? 3 : 2) void attn_bwd_dq_kernel(BwdParams p) {
   using G = BGeo<D>;
   constexpr int KB = 64, NKT = KB / 32, NT = NW * 64, FT = NT / 2;
   constexpr int TCH = KB * G::CH;
@@ -442,10 +449,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 2) void attn_bwd_dq_kernel(B
         }
       }
     };
-    // 4 waves: one tile at a time, whose fewer live scores (168 registers) leave
-    // room for three work-groups on a CU instead of two
     using std::integral_constant;
-    if constexpr (NW == 4) {
+    if constexpr (ONE) {
       keys(integral_constant<int, 0>{}, integral_constant<int, 1>{});
       keys(integral_constant<int, 1>{}, integral_constant<int, 2>{});
     } else {
@@ -915,9 +920,7 @@ void fill_common(P& p, const AttnBwdArgs& a) {
 // of self-attention (D = 72, 16 to 640 units, 150 to 3000 rows, both kernels together,
 // relative error 5-7%).  Choosing by it is within 0.3% of the better one on average and
 // takes 9% off what 8 waves need: 34 frames of 400 tokens (16 heads) 194 -> 165 us, 7 x
-// 1350 290 -> 270, 16 units of 1024 67 -> 54.  `four`: what 4 waves cost against the fit;
-// dQ 0.94 since a CU holds three of its work-groups (32 x 1024 forward and backward 857
-// -> 840 us).
+// 1350 290 -> 270, 16 units of 1024 67 -> 54.  `four`: what 4 waves cost against the fit.
 int bwd_waves(int64_t units, int64_t rows, int64_t tiles, double four) {
   struct Shape {
     int waves, levels;
@@ -938,6 +941,23 @@ int bwd_waves(int64_t units, int64_t rows, int64_t tiles, double four) {
   return four * cost[1] < cost[0] ? 4 : 8;
 }
 
+// What four waves cost dQ against the fit: 0.94 where a CU holds three of their
+// work-groups (D = 72, 32 x 1024 forward and backward 857 -> 840 us).  Narrow heads have
+// that gain only over several tiles (D = 32, 512 units of 150 keys: 26.5 us with eight waves,
+// 27.5 with four).
+double dq_four(int D, int64_t tiles) { return dq_one_tile(D) && (D >= 64 || tiles >= 6) ? 0.94 : 1.0; }
+
+struct BwdWaves {
+  int dq, dkv;
+};
+// Waves per work-group of the two kernels (units longer than the fused kernel takes).
+BwdWaves choose_bwd_waves(int D, int64_t bx, int H, int Hkv, int64_t L, int64_t Lk) {
+  if (std::max(L, Lk) <= 64) return {2, 2};
+  if (std::max(L, Lk) <= 128) return {4, 4};
+  const int64_t q_tiles = (L + 63) / 64, k_tiles = (Lk + 63) / 64;
+  return {bwd_waves(bx * H, L, k_tiles, dq_four(D, k_tiles)), bwd_waves(bx * Hkv, Lk, (H / Hkv) * q_tiles, 1.0)};
+}
+
 template <int D, int NW>
 int launch_dq(BwdParams p, const AttnBwdArgs& a, hipStream_t s) {
   // query heads x blocks of 32 NW queries
@@ -945,7 +965,17 @@ int launch_dq(BwdParams p, const AttnBwdArgs& a, hipStream_t s) {
   if (blocks >= (int64_t(1) << 31)) return DSP_ERR_SHAPE;
   p.n_blk = (uint32_t)nq;
   p.n_blocks = (uint32_t)blocks;
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW>), dim3((uint32_t)blocks), dim3(NW * 64), 0, s, p);
+  const dim3 grid((uint32_t)blocks), block(NW * 64);
+  // Short units (grouped heads of 65 to 128 positions) of at most two work-groups per CU
+  // gain nothing from a third: two tiles at once, 2% faster there (D = 72, 64 units of
+  // 100: 18.5 against 18.9 us).
+  if constexpr (NW == 4 && dq_one_tile(D)) {
+    if (std::max(a.L, a.Lk) > 128 || blocks > 512) {
+      hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, true>), grid, block, 0, s, p);
+      return last_launch_status();
+    }
+  }
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, false>), grid, block, 0, s, p);
   return last_launch_status();
 }
 
@@ -1036,14 +1066,16 @@ int launch_bwd_d(const AttnBwdArgs& a, hipStream_t s) {
     return launch_bwd_short<D, 4>(a, s);
   }
 #endif
-  if (L <= 64) return launch_bwd_two<D>(a, 2, 2, s);
-  if (L <= 128) return launch_bwd_two<D>(a, 4, 4, s);
-  const int64_t bx = a.B * a.X;
-  return launch_bwd_two<D>(a, bwd_waves(bx * a.H, a.L, (a.Lk + 63) / 64, 0.94),
-                           bwd_waves(bx * a.Hkv, a.Lk, (a.H / a.Hkv) * ((a.L + 63) / 64), 1.0), s);
+  const BwdWaves w = choose_bwd_waves(D, a.B * a.X, a.H, a.Hkv, a.L, a.Lk);
+  return launch_bwd_two<D>(a, w.dq, w.dkv, s);
 }
 
 }  // namespace
+
+extern "C" int dsp_choice_attn_bwd(int D, int64_t bx, int H, int Hkv, int64_t L, int64_t Lk) {
+  const BwdWaves w = choose_bwd_waves(D, bx, H, Hkv, L, Lk);
+  return w.dq | w.dkv << 8;
+}
 
 bool attn_bwd_bf16_fits(const AttnBwdArgs& a) {
   // block indices, and the byte ranges of a 64-row tile, are 32-bit

@@ -179,6 +179,9 @@ inline int64_t grid_blocks(int threads) { return ((int64_t(1) << 32) / threads -
 // name the variant they mean to run.
 //   Queries per work-group of the bf16 attention forward.
 extern "C" int dsp_choice_attn_fwd(int D, int64_t units, int64_t L, int64_t Lk, int64_t q_row_stride);
+//   Waves per work-group of the bf16 attention gradients' two kernels (units of more
+// than 128 positions, or grouped heads): dQ | dK/dV << 8; bx: units per head.
+extern "C" int dsp_choice_attn_bwd(int D, int64_t bx, int H, int Hkv, int64_t L, int64_t Lk);
 //   Output tile of the bf16 GEMM, rows << 16 | columns (| 1 << 31: four K slices in
 // flight where two are usual), for the plain GELU epilogue or another.
 extern "C" uint32_t dsp_choice_linear(int64_t M, int64_t N, int64_t K, int gelu);

@@ -32,6 +32,24 @@ def test_attention_forward_grid(L, Lk):
         assert units * -(-L // q) * threads[q] < GRID_THREADS, (units, q)
 
 
+def attn_bwd(D, bx, H, Hkv, L, Lk):
+    """(waves of dQ, waves of dK/dV) per work-group"""
+    f = dsp.lib().dsp_choice_attn_bwd
+    f.restype, f.argtypes = INT, [INT, I64, INT, INT, I64, I64]
+    v = f(D, bx, H, Hkv, L, Lk)
+    return v & 255, v >> 8
+
+
+def test_attention_backward_waves_near_ties():
+    """Four and eight waves within a few percent of each other: four only at the head
+    widths, and over the tiles, where three of their work-groups share a CU."""
+    assert attn_bwd(80, 128, 4, 4, 150, 150) == (8, 8)
+    assert attn_bwd(80, 512, 4, 4, 1024, 1024) == (8, 8)
+    assert attn_bwd(32, 128, 4, 4, 150, 150) == (8, 8)
+    assert attn_bwd(72, 128, 4, 4, 150, 150) == (4, 8)
+    assert attn_bwd(72, 512, 4, 4, 1024, 1024) == (4, 8)
+
+
 def linear(M, N, K, gelu=False):
     """(rows, columns, whether four K slices are in flight) of the output tile"""
     f = dsp.lib().dsp_choice_linear
