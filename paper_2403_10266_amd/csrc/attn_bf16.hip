@@ -817,16 +817,24 @@ int choose_queries_many_keys(int64_t units, int64_t L, int64_t Lk) {
 
 // Queries per work-group for at most 32 keys: one wave and a 32-key tile suit few
 // queries (150: 13.0 against 15.0 us for 800 units), four waves on a half-empty
-// 64-key tile many (1024: 45 -> 33 us, 300: 5.4 -> 5.1 for 32 units).  Rows too far
-// apart for a block of 128 run in blocks of 32, and so do units too many for a grid
-// of four-wave blocks (257 queries are 768 threads that way, 576 in blocks of 32).
-int choose_queries_few_keys(int64_t units, int64_t L, int64_t row_stride) {
-  return L >= 256 && rows_fit(L, 128, row_stride) && grid_fits(units * ((L + 127) / 128), 256) ? 128 : 32;
+// 64-key tile many (D = 72: 1024 queries 45 -> 33 us, 300 17.1 -> 15.3, both for 512
+// units).  Against the one-wave tiling, 4 to 2048 units of 257 to 4096 queries:
+//   D = 16 never gains (257 of 2048 units 14.8 against 20.0 us);
+//   D = 32 does from 1024 queries and 2^18 in all (81 -> 68 us; 2^17 7.7 against 8.0);
+//   D = 64 and 72 from 256 queries on (0.98 to 1.66 times as fast);
+//   D = 80 and 96 from 2^16 in all (222 -> 162 us; 2^15 at 96 8.2 against 9.1).
+// Rows too far apart for a block of 128 run in blocks of 32, and so do units too many
+// for a grid of four-wave blocks (257 queries are 768 threads that way, 576 in blocks
+// of 32).
+int choose_queries_few_keys(int D, int64_t units, int64_t L, int64_t row_stride) {
+  const int64_t total = units * L;
+  const bool many = D < 32 ? false : D == 32 ? L >= 1024 && total >= (1 << 18) : L >= 256 && (D <= 72 || total >= (1 << 16));
+  return many && rows_fit(L, 128, row_stride) && grid_fits(units * ((L + 127) / 128), 256) ? 128 : 32;
 }
 
 // Queries per work-group of a launch.
-int choose_queries(int64_t units, int64_t L, int64_t Lk, int64_t row_stride) {
-  if (Lk <= 32) return choose_queries_few_keys(units, L, row_stride);
+int choose_queries(int D, int64_t units, int64_t L, int64_t Lk, int64_t row_stride) {
+  if (Lk <= 32) return choose_queries_few_keys(D, units, L, row_stride);
   if (Lk <= 64) return 64;
   if (Lk <= 128) return DSP_TATTN_NW * DSP_TATTN_QT * 32;
   return choose_queries_many_keys(units, L, Lk);
@@ -836,7 +844,7 @@ template <int D>
 int launch_d(const AttnArgs& a, hipStream_t s) {
   // few keys: all of a unit's keys are one tile, fetched at once (the tiling
   // is chosen by the key count; any number of queries runs in query blocks)
-  const int queries = choose_queries(a.B * a.X * a.H, a.L, a.Lk, a.r_stride_in);
+  const int queries = choose_queries(D, a.B * a.X * a.H, a.L, a.Lk, a.r_stride_in);
   if (a.Lk <= 32) {
     if (queries == 128) return launch_cfg<D, 4, 1, 64, 3, 1>(a, s);
     return launch_cfg<D, 1, 1, 32, 1, 1>(a, s);
@@ -859,7 +867,7 @@ int launch_d(const AttnArgs& a, hipStream_t s) {
 }  // namespace
 
 extern "C" int dsp_choice_attn_fwd(int D, int64_t units, int64_t L, int64_t Lk, int64_t q_row_stride) {
-  return attn_bf16_supports(D) ? choose_queries(units, L, Lk, q_row_stride) : 0;
+  return attn_bf16_supports(D) ? choose_queries(D, units, L, Lk, q_row_stride) : 0;
 }
 
 bool attn_bf16_supports(int D) {

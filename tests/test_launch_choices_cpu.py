@@ -23,13 +23,23 @@ ATTN_THREADS = {"many": {512: 512, 256: 256, 128: 256}, "few": {128: 256, 32: 64
 
 @pytest.mark.parametrize("L", [256, 257, 300, 512, 1000, 4096])
 @pytest.mark.parametrize("Lk", [1, 20, 32, 129, 300, 1000])
-def test_attention_forward_grid(L, Lk):
+@pytest.mark.parametrize("D", [16, 72])
+def test_attention_forward_grid(L, Lk, D):
     kind = "few" if Lk <= 32 else "many"
     threads, base = ATTN_THREADS[kind], 32 if Lk <= 32 else 512
     most = (GRID_THREADS - 1) // (-(-L // base) * threads[base])    # units that blocks of `base` queries can launch
     for units in (most, most - 1, most * 3 // 4, most // 2 + 1, most // 2):
-        q = attn_fwd(16, units, L, Lk)
+        q = attn_fwd(D, units, L, Lk)
         assert units * -(-L // q) * threads[q] < GRID_THREADS, (units, q)
+
+
+@pytest.mark.parametrize("D,units,L,queries", [
+    (16, 2048, 4096, 32), (32, 512, 257, 32), (32, 512, 1023, 32), (32, 128, 1024, 32), (32, 256, 1024, 128),
+    (64, 1, 256, 128), (72, 4, 257, 128), (72, 4, 255, 32), (80, 32, 1024, 32), (80, 64, 1024, 128), (96, 128, 257, 32),
+    (96, 512, 257, 128),
+])
+def test_attention_forward_few_keys(D, units, L, queries):
+    assert attn_fwd(D, units, L, 20) == queries
 
 
 def attn_bwd(D, bx, H, Hkv, L, Lk):
