@@ -786,21 +786,27 @@ int launch_cfg(const AttnArgs& a, hipStream_t s) {
 // costs 0.9% on average against each shape's best of the three and takes 23% off what
 // 512 queries need: 7 x 1350 (16 heads) 96 -> 80 us, 60 x 250 57 -> 37, 34 x 400 62 -> 50;
 // 32 x 1024 and 32 x 4096 stay on 512 (180 against 183, 2330 against 2410 us with 256).
+// At D = 96 blocks of 256 are left out: they spill registers (512 units of 2000 queries on
+// 500 keys 267 us with 512, 364 with 256; 150 x 150 is faster with 128).  Over D = 80 and 96,
+// 4 to 2048 units and 150 to 4096 queries and keys the choice is then never slower than 512
+// by more than the runs differ.
 struct QueryBlock {
   int queries, levels;
   double a[3], b[3];
 };
 constexpr int kMaxQueryBlock = 512;
+constexpr int kMaxD256 = 80;  // widest head of the 256-query blocks
 constexpr QueryBlock kSmallBlocks[2] = {{256, 2, {1.4, 4.8}, {1.38, 2.20}},
                                         {128, 3, {0.4, 2.2, 3.8}, {0.90, 1.35, 1.84}}};
 
-int choose_queries_many_keys(int64_t units, int64_t L, int64_t Lk) {
+int choose_queries_many_keys(int D, int64_t units, int64_t L, int64_t Lk) {
   const double tiles = (double)((Lk + 63) / 64);
   const int64_t rounds = (units * ((L + kMaxQueryBlock - 1) / kMaxQueryBlock) + 255) / 256;
   int best = kMaxQueryBlock;
   double best_cost = rounds == 1 ? 6.2 + 1.93 * tiles : (double)rounds * (7.1 + 2.09 * tiles);
   for (const QueryBlock& q : kSmallBlocks) {
     const int64_t blocks = units * ((L + q.queries - 1) / q.queries), round = 256 * q.levels, rest = blocks % round;
+    if (q.queries == 256 && D > kMaxD256) continue;
     if (!grid_fits(blocks, 256)) continue;  // both have four waves: up to twice the threads of 512
     double cost = 3.9 + (double)(blocks / round) * (q.a[q.levels - 1] + q.b[q.levels - 1] * tiles);
     if (rest) {
@@ -822,13 +828,14 @@ int choose_queries_many_keys(int64_t units, int64_t L, int64_t Lk) {
 //   D = 16 never gains (257 of 2048 units 14.8 against 20.0 us);
 //   D = 32 does from 1024 queries and 2^18 in all (81 -> 68 us; 2^17 7.7 against 8.0);
 //   D = 64 and 72 from 256 queries on (0.98 to 1.66 times as fast);
-//   D = 80 and 96 from 2^16 in all (222 -> 162 us; 2^15 at 96 8.2 against 9.1).
+//   D = 80 and 96 from 2^17 in all (222 -> 162 us; 2^16 at 96 9.9 against 10.3).
 // Rows too far apart for a block of 128 run in blocks of 32, and so do units too many
 // for a grid of four-wave blocks (257 queries are 768 threads that way, 576 in blocks
 // of 32).
+constexpr int kMinDFewKeys = 32;
 int choose_queries_few_keys(int D, int64_t units, int64_t L, int64_t row_stride) {
   const int64_t total = units * L;
-  const bool many = D < 32 ? false : D == 32 ? L >= 1024 && total >= (1 << 18) : L >= 256 && (D <= 72 || total >= (1 << 16));
+  const bool many = D < kMinDFewKeys ? false : D == 32 ? L >= 1024 && total >= (1 << 18) : L >= 256 && (D <= 72 || total >= (1 << 17));
   return many && rows_fit(L, 128, row_stride) && grid_fits(units * ((L + 127) / 128), 256) ? 128 : 32;
 }
 
@@ -837,7 +844,7 @@ int choose_queries(int D, int64_t units, int64_t L, int64_t Lk, int64_t row_stri
   if (Lk <= 32) return choose_queries_few_keys(D, units, L, row_stride);
   if (Lk <= 64) return 64;
   if (Lk <= 128) return DSP_TATTN_NW * DSP_TATTN_QT * 32;
-  return choose_queries_many_keys(units, L, Lk);
+  return choose_queries_many_keys(D, units, L, Lk);
 }
 
 template <int D>
@@ -846,7 +853,8 @@ int launch_d(const AttnArgs& a, hipStream_t s) {
   // is chosen by the key count; any number of queries runs in query blocks)
   const int queries = choose_queries(D, a.B * a.X * a.H, a.L, a.Lk, a.r_stride_in);
   if (a.Lk <= 32) {
-    if (queries == 128) return launch_cfg<D, 4, 1, 64, 3, 1>(a, s);
+    if constexpr (D >= kMinDFewKeys)
+      if (queries == 128) return launch_cfg<D, 4, 1, 64, 3, 1>(a, s);
     return launch_cfg<D, 1, 1, 32, 1, 1>(a, s);
   }
   if (a.Lk <= 64) return launch_cfg<D, 2, 1, 64, 2, 1>(a, s);
@@ -857,11 +865,10 @@ int launch_d(const AttnArgs& a, hipStream_t s) {
       return launch_cfg<D, DSP_TATTN_NW, DSP_TATTN_QT, DSP_TATTN_KB, DSP_TATTN_MINW>(a, s);
   }
   static_assert(DSP_SATTN_NW * DSP_SATTN_QT * 32 == kMaxQueryBlock, "the largest query block");
-  switch (queries) {
-    case 256: return launch_cfg<D, 4, 2, 64, 2>(a, s);
-    case 128: return launch_cfg<D, 4, 1, 64, 3>(a, s);
-    default: return launch_cfg<D, DSP_SATTN_NW, DSP_SATTN_QT, DSP_SATTN_KB, DSP_SATTN_MINW>(a, s);
-  }
+  if constexpr (D <= kMaxD256)
+    if (queries == 256) return launch_cfg<D, 4, 2, 64, 2>(a, s);
+  if (queries == 128) return launch_cfg<D, 4, 1, 64, 3>(a, s);
+  return launch_cfg<D, DSP_SATTN_NW, DSP_SATTN_QT, DSP_SATTN_KB, DSP_SATTN_MINW>(a, s);
 }
 
 }  // namespace

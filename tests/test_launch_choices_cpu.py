@@ -35,11 +35,19 @@ def test_attention_forward_grid(L, Lk, D):
 
 @pytest.mark.parametrize("D,units,L,queries", [
     (16, 2048, 4096, 32), (32, 512, 257, 32), (32, 512, 1023, 32), (32, 128, 1024, 32), (32, 256, 1024, 128),
-    (64, 1, 256, 128), (72, 4, 257, 128), (72, 4, 255, 32), (80, 32, 1024, 32), (80, 64, 1024, 128), (96, 128, 257, 32),
+    (64, 1, 256, 128), (72, 4, 257, 128), (72, 4, 255, 32), (80, 64, 1024, 32), (80, 128, 1024, 128), (96, 128, 257, 32),
     (96, 512, 257, 128),
 ])
 def test_attention_forward_few_keys(D, units, L, queries):
     assert attn_fwd(D, units, L, 20) == queries
+
+
+def test_attention_forward_widest_head():
+    """At D = 96 the 256-query instance spills registers: never chosen."""
+    for units in (4, 32, 128, 512, 2048):
+        for L, Lk in ((150, 150), (300, 300), (512, 129), (1024, 300), (2000, 500)):
+            assert attn_fwd(96, units, L, Lk) != 256
+    assert attn_fwd(72, 512, 2000, 500) == 256
 
 
 def attn_bwd(D, bx, H, Hkv, L, Lk):
