@@ -55,8 +55,8 @@ struct ParamsF {
   float* delta;
   int64_t b_q, x_q, r_q, b_kv, x_kv, r_kv, b_o, x_o, r_o;
   int64_t X, H, L, Lk, grp, D, n_dc;
-  int64_t n_blk;  // row blocks per unit
-  int64_t first;  // this launch's first block
+  uint32_t n_blk;  // row blocks per unit
+  int64_t first;   // this launch's first unit
   float scale;
   bool vec;       // every row starts on 16 bytes and D is a multiple of 4
 };
@@ -90,11 +90,14 @@ struct RowTile {
   static constexpr int LOADS = (32 * CPR + NTHR - 1) / NTHR;
   static constexpr int ELEMS = 32 * P + 32;  // d-row reads of the last row run up to 32 floats on (results dropped)
   float4 pre[LOADS];
+  // REPEAT: the last row fills up the group of 8 that d-row products read with it
+  template <bool REPEAT = false>
   __device__ __forceinline__ void load(const float* base, int64_t stride, int64_t rows, int64_t D, bool vec) {
+    const int last = (int)min(rows, (int64_t)32) - 1, end = REPEAT ? last | 7 : last;
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
       const int e = (int)threadIdx.x + NTHR * i, r = e / CPR, c = (e % CPR) * 4;
-      pre[i] = load4(base + r * stride + c, (32 * CPR % NTHR == 0 || r < 32) && r < rows ? D - c : 0, vec);
+      pre[i] = load4(base + (REPEAT ? min(r, last) : r) * stride + c, r <= end ? D - c : 0, vec);
     }
   }
   __device__ __forceinline__ void store(float* lds) const {
@@ -164,9 +167,9 @@ __device__ __forceinline__ void store_own(float* row, const floatx16 (&acc)[NT],
 
 // The work-group's block of a unit's rows: units in contiguous ranges per XCD
 // (their tiles are then shared through one L2).
-__device__ __forceinline__ int64_t xcd_block(int64_t first) {
+__device__ __forceinline__ uint32_t xcd_block() {
   const uint32_t n = gridDim.x, per = n >> 3, extra = n & 7u, xcd = blockIdx.x & 7u;
-  return first + (xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3));
+  return xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
 }
 
 template <int DP, int NW>
@@ -181,8 +184,8 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_mfma_kernel(ParamsF p) {
   constexpr int NB = G::NB, NT = G::NT, TE = G::Tile::ELEMS;
   __shared__ __attribute__((aligned(16))) float lds[NB * 2 * TE];
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
-  const int64_t blk = xcd_block(p.first);
-  const int64_t unit = blk / p.n_blk, qi = (blk % p.n_blk) * (32 * NW) + 32 * (threadIdx.x >> 6) + l32;
+  const uint32_t blk = xcd_block();
+  const int64_t unit = p.first + blk / p.n_blk, qi = (int64_t)(blk % p.n_blk) * (32 * NW) + 32 * (threadIdx.x >> 6) + l32;
   const int64_t h = unit % p.H, bx = unit / p.H, xx = bx % p.X, bb = bx / p.X;
   const bool valid = qi < p.L;
   float4 q[DP / 8];
@@ -255,8 +258,8 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dq_mfma_kernel(ParamsF p
   constexpr int NB = G::NB, NT = G::NT, TE = G::Tile::ELEMS;
   __shared__ __attribute__((aligned(16))) float lds[NB * 2 * TE];
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
-  const int64_t blk = xcd_block(p.first);
-  const int64_t unit = blk / p.n_blk, qi = (blk % p.n_blk) * (32 * NW) + 32 * (threadIdx.x >> 6) + l32;
+  const uint32_t blk = xcd_block();
+  const int64_t unit = p.first + blk / p.n_blk, qi = (int64_t)(blk % p.n_blk) * (32 * NW) + 32 * (threadIdx.x >> 6) + l32;
   const int64_t h = unit % p.H, bx = unit / p.H, xx = bx % p.X, bb = bx / p.X;
   const bool valid = qi < p.L;
   const int64_t qb = bb * p.b_q + xx * p.x_q + h * p.D + qi * p.r_q;
@@ -322,9 +325,9 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dkv_mfma_kernel(ParamsF 
   constexpr int NB = G::NB, NT = G::NT, TE = G::Tile::ELEMS;
   __shared__ __attribute__((aligned(16))) float lds[NB * (2 * TE + 64)];
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
-  const int64_t blk = xcd_block(p.first);
+  const uint32_t blk = xcd_block();
   const int64_t Hkv = p.H / p.grp;
-  const int64_t unit = blk / p.n_blk, key = (blk % p.n_blk) * (32 * NW) + 32 * (threadIdx.x >> 6) + l32;
+  const int64_t unit = p.first + blk / p.n_blk, key = (int64_t)(blk % p.n_blk) * (32 * NW) + 32 * (threadIdx.x >> 6) + l32;
   const int64_t hk = unit % Hkv, bx = unit / Hkv, xx = bx % p.X, bb = bx / p.X;
   const bool valid = key < p.Lk;
   const int64_t kvb = bb * p.b_kv + xx * p.x_kv + hk * p.D + key * p.r_kv;
@@ -340,10 +343,13 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dkv_mfma_kernel(ParamsF 
   const int64_t n_q = (p.L + 31) / 32, n = p.grp * n_q;
   auto fetch = [&](int64_t i) {
     const int64_t hq = hk * p.grp + i / n_q, r0 = (i % n_q) * 32;
-    qt.load(p.q + bb * p.b_q + xx * p.x_q + hq * p.D + r0 * p.r_q, p.r_q, p.L - r0, p.D, p.vec);
+    // (Q rows past L repeat a real row: against zeros the score of an infinite key, and with it
+    // the probability, would be NaN)
+    qt.template load<true>(p.q + bb * p.b_q + xx * p.x_q + hq * p.D + r0 * p.r_q, p.r_q, p.L - r0, p.D, p.vec);
     dt.load(p.dout + bb * p.b_o + xx * p.x_o + hq * p.D + r0 * p.r_o, p.r_o, p.L - r0, p.D, p.vec);
     if (threadIdx.x < 64) {
       const int64_t r = r0 + l32, at = (bx * p.H + hq) * p.L + r;
+      // rows past L: lse +inf, so their probabilities are 0
       stat = threadIdx.x < 32 ? (r < p.L ? p.lse[at] : INFINITY) : (r < p.L ? p.delta[at] : 0.0f);
     }
   };
@@ -360,7 +366,6 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dkv_mfma_kernel(ParamsF 
     __syncthreads();
     if (i + 1 < n) fetch(i + 1);
     if (NB == 2) buf ^= 1;
-    const int64_t left = p.L - (i % n_q) * 32;
     floatx16 s[2];
     zero(s);
 #pragma unroll
@@ -378,10 +383,9 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dkv_mfma_kernel(ParamsF 
         const int r = 4 * r4 + e;
         s[0][r] = expf(s[0][r] * p.scale - lv[e]);
         s[1][r] = s[0][r] * (s[1][r] - dl[e]);
-        // rows past L hold zeros, which an infinite key or value makes NaN
-        if (left < 32 && 8 * r4 + 4 * g + e >= left) s[0][r] = s[1][r] = 0.0f;
       }
     }
+    const int64_t left = p.L - (i % n_q) * 32;
     drow_product<DP, NT>(ds, s[0], left, l32, g, dv);
     drow_product<DP, NT>(qs, s[1], left, l32, g, dk);
   }
@@ -528,14 +532,13 @@ void launch_mfma(Which which, const ParamsF& p, uint32_t blocks, hipStream_t s) 
 // One kernel over `units` units of `rows` owned rows each.
 int launch_units(Which which, ParamsF p, int64_t units, int64_t rows, hipStream_t s) {
   const int nw = rows <= 32 ? 1 : 4;
-  p.n_blk = (rows + 32 * nw - 1) / (32 * nw);
-  const int64_t blocks = units * p.n_blk;
+  const int64_t n_blk = (rows + 32 * nw - 1) / (32 * nw), most = grid_blocks(64 * nw) / n_blk;  // units of one grid
   const int dp = padded_width(p.D);
-  if (dp) {
+  if (dp && most > 0) {
     // one launch, or several where the threads are too many for a grid
-    const int64_t most = grid_blocks(64 * nw);
-    for (p.first = 0; p.first < blocks; p.first += most) {
-      const uint32_t n = (uint32_t)std::min(most, blocks - p.first);
+    p.n_blk = (uint32_t)n_blk;
+    for (p.first = 0; p.first < units; p.first += most) {
+      const uint32_t n = (uint32_t)(std::min(most, units - p.first) * n_blk);
 #define DSP_F32_CASE(DP_)                                                                            \
   case DP_:                                                                                          \
     nw == 1 ? launch_mfma<DP_, 1>(which, p, n, s) : launch_mfma<DP_, 4>(which, p, n, s);             \
