@@ -17,13 +17,19 @@
 //    the A operand is read from the same LDS rows, 32 consecutive floats a half.
 //  * Softmax statistics are per lane (one swap across the halves); the running
 //    maximum is exact and a move rescales the accumulators.
-//  * 4 waves (128 rows) share a work-group's tiles; 1 wave when there are at most
-//    32 rows, with one LDS buffer instead of two so that more groups fit a CU.
+//  * 4 waves (128 rows) share a work-group's tiles, in the forward 2 where 64 rows do;
+//    1 wave when there are at most 32 rows, with one LDS buffer instead of two so that
+//    more groups fit a CU.
+// Registers, not LDS, set the occupancy (one or two waves per SIMD from D = 64 on), and
+// the one-wave kernels, whose wave fetches whole tiles alone, run out of them in dK/dV:
+// 10 spilled at D = 72 (44 bytes a lane), 134 at 96, 627 at 128 (four waves: 140).
 // Measured (16 heads of 72): 8 frames of L = 256 forward 47 us (51 TFLOP/s), dQ 55
 // and dK/dV 68 us; before, one wave walking a unit's keys with plain FMAs took
 // 1095 us and the gradients, one thread per row and 32 columns, 9.7 + 10.7 ms.
 // 256 units of L = 8: 31 (34) us forward, 90 (625) us backward.
 //
+// A few keys (wave_per_unit, thread_per_row below) are a fraction of a 32-row tile: the
+// forward then runs plain FMAs, a wave per unit or a thread per row.
 // Wider heads run the general kernels at the end: one thread per (unit, row,
 // 32-column slice of the output), plain FMAs.
 #include <math.h>
@@ -36,6 +42,10 @@ namespace dsp {
 namespace {
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
+
+// Where a running maximum starts: finite, so that scores of -inf have probability 0
+// (not NaN) before a row's first finite one.
+constexpr float kLowest = -3.402823466e38f;
 
 constexpr int DC = 32;  // output columns per thread of the general kernels
 
@@ -198,7 +208,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_mfma_kernel(ParamsF p) {
   vt.load(vg, p.r_kv, p.Lk, p.D, p.vec);
   floatx16 o[NT];
   zero(o);
-  float m = -INFINITY, l = 0.0f;
+  float m = kLowest, l = 0.0f;
   int buf = 0;
   for (int64_t k0 = 0; k0 < p.Lk; k0 += 32) {
     float* ks = lds + buf * 2 * TE;
@@ -225,8 +235,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_mfma_kernel(ParamsF p) {
     }
     mt = fmaxf(mt, other_half(mt));
     if (__any(mt > m)) {
-      // corr is 0 for the first tile, and 1 for a row whose scores are all -inf so far
-      const float mn = fmaxf(m, mt), corr = m == mn ? 1.0f : expf(m - mn);
+      const float mn = fmaxf(m, mt), corr = expf(m - mn);  // 0 for the first tile
       l *= corr;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
@@ -235,17 +244,16 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_mfma_kernel(ParamsF p) {
       m = mn;
     }
     float sum = 0.0f;
-    const float ref = m == -INFINITY ? 0.0f : m;  // no finite score yet: probabilities 0, not NaN
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[0][r] = expf(s[0][r] - ref);
+      s[0][r] = expf(s[0][r] - m);
       sum += s[0][r];
     }
     l += sum;
     drow_product<DP, NT>(vs, s[0], p.Lk - k0, l32, g, o);
   }
   l += other_half(l);
-  if (m == -INFINITY) l = NAN;  // a softmax over scores that are all -inf
+  if (l == 0.0f) l = NAN;  // a softmax over scores that are all -inf
   if (!valid) return;
   store_own<NT>(p.out_o + bb * p.b_o + xx * p.x_o + h * p.D + qi * p.r_o, o, p.D, p.vec, g, 1.0f / l);
   if (p.out_lse && g == 0) p.out_lse[unit * p.L + qi] = m + logf(l);
@@ -394,6 +402,72 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_dkv_mfma_kernel(ParamsF 
   store_own<NT>(p.dv + kvb, dv, p.D, p.vec, g, 1.0f);
 }
 
+// ---------------------------------------------------------------- few keys
+// Forward, one wave per unit, plain FMAs: lanes own queries lane, lane + 64, .. with the
+// query row and the D output columns in registers, the keys and values pass through
+// LDS in chunks of 32 rows (every lane reads the same row: a broadcast), and the softmax
+// runs online.  A few keys are a fraction of the 32-row tile the matrix instructions
+// work through, and this kernel moves only the rows there are.
+template <int D>
+__global__ __launch_bounds__(64) void attn_f32_unit_kernel(ParamsF p) {
+  constexpr int KC = 32;
+  __shared__ __attribute__((aligned(16))) float ks[KC * D];
+  __shared__ __attribute__((aligned(16))) float vs[KC * D];
+  const int lane = threadIdx.x;
+  const int64_t unit = p.first + blockIdx.x;
+  const int64_t h = unit % p.H, bx = unit / p.H, xx = bx % p.X, bb = bx / p.X;
+  const float* qg = p.q + bb * p.b_q + xx * p.x_q + h * D;
+  const int64_t kvb = bb * p.b_kv + xx * p.x_kv + (h / p.grp) * D;
+  const float *kg = p.k + kvb, *vg = p.v + kvb;
+  float* og = p.out_o + bb * p.b_o + xx * p.x_o + h * D;
+  for (int64_t q0 = 0; q0 < p.L; q0 += 64) {
+    const int64_t qi = q0 + lane;
+    const bool valid = qi < p.L;
+    float qr[D], acc[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      qr[d] = valid ? qg[qi * p.r_q + d] : 0.0f;
+      acc[d] = 0.0f;
+    }
+    float m = kLowest, l = 0.0f;
+    for (int64_t k0 = 0; k0 < p.Lk; k0 += KC) {
+      const int nk = (int)min((int64_t)KC, p.Lk - k0);
+      __syncthreads();  // the previous chunk is consumed
+      for (int e = lane; e < nk * D; e += 64) {
+        const int r = e / D, c = e - r * D;
+        ks[e] = kg[(k0 + r) * p.r_kv + c];
+        vs[e] = vg[(k0 + r) * p.r_kv + c];
+      }
+      __syncthreads();
+      for (int j = 0; j < nk; ++j) {
+        float sc = 0.0f;
+#pragma unroll
+        for (int d = 0; d < D; ++d) sc = fmaf(qr[d], ks[j * D + d], sc);
+        sc *= p.scale;
+        if (sc > m) {
+          const float corr = expf(m - sc);  // 0 for the first key
+          l *= corr;
+#pragma unroll
+          for (int d = 0; d < D; ++d) acc[d] *= corr;
+          m = sc;
+        }
+        const float e = expf(sc - m);
+        l += e;
+#pragma unroll
+        for (int d = 0; d < D; ++d) acc[d] = fmaf(e, vs[j * D + d], acc[d]);
+      }
+    }
+    if (l == 0.0f) l = NAN;  // a softmax over scores that are all -inf
+    if (valid) {
+      const float inv = 1.0f / l;
+      float* orow = og + qi * p.r_o;
+#pragma unroll
+      for (int d = 0; d < D; ++d) orow[d] = acc[d] * inv;
+      if (p.out_lse) p.out_lse[unit * p.L + qi] = m + logf(l);
+    }
+  }
+}
+
 // ---------------------------------------------------------------- general kernels (any head width)
 
 __device__ __forceinline__ float dotf(const float* a, const float* b, int64_t n) {
@@ -514,15 +588,49 @@ bool rows_al16(const void* p, const int64_t st[3]) {
 }
 
 // The padded head width whose instance takes width D (0: none).
-int padded_width(int64_t D) { return D <= 32 ? 32 : D <= 64 ? 64 : D <= 72 ? 72 : D <= 96 ? 96 : D <= 128 ? 128 : 0; }
+int padded_width(int64_t D) { return D <= 16 ? 16 : D <= 32 ? 32 : D <= 64 ? 64 : D <= 72 ? 72 : D <= 96 ? 96 : D <= 128 ? 128 : 0; }
+
+// Whether the forward runs a wave per unit.  Times (wave per unit / matrix kernel, us),
+// units of L = Lk rows:
+//   D = 72: 1024 units of 3 rows 8 / 9, of 4 9 / 9; 8192 of 4 36 / 54, of 6 47 / 54, of 8 60 / 56;
+//   D = 96: 8192 of 4 59 / 62; D = 32: 1024 of 4 6 / 6, 8192 of 6 17 / 22, of 8 21 / 22, of 10 26 / 24;
+//   D = 16: 8192 of 8 14 / 14, of 33 42 / 46; 32768 of 8 34 / 44, of 33 120 / 165, of 64 on 300 keys 888 / 956,
+//   of 65 413 / 517.
+// At D = 16 the matrix tiles' padding also decides for many longer units: 32-row waves
+// and 32-key tiles against 64-row waves and single keys.
+bool wave_per_unit(int64_t D, int64_t units, int64_t L, int64_t Lk) {
+  if (D != 16 && D != 32 && D != 64 && D != 72 && D != 80 && D != 96) return false;
+  if (L <= 64 && Lk <= (D <= 32 ? 4 : 3)) return true;
+  if (L <= 64 && units >= 2048 && Lk <= (D <= 32 ? 8 : D <= 80 ? 6 : 4)) return true;
+  if (L <= 64 && units >= 16384 && D <= 32 && Lk <= 10) return true;
+  if (D > 16 || units < 8192 || L <= 32 || L > 256) return false;
+  const int64_t waves = L <= 64 ? 2 : (L + 127) / 128 * 4;  // of the matrix kernel
+  return 2 * ((L + 63) / 64) * Lk * 100 <= 95 * waves * ((Lk + 31) / 32) * 32;
+}
+
+// Whether the forward's general kernel (a thread per row and 32 columns) is the faster
+// one at the other widths: a few keys of very many short units.  (general / matrix, us)
+// D = 40: 4096 units of one row 18 / 24, 8192 of 3 37 / 45, 32768 of 4 240 / 167; D = 24: 8192 of
+// one 20 / 22, 32768 of 2 34 / 72; D = 8: 8192 of 4 11 / 14, of 5 15 / 14, 32768 of 6 36 / 44.
+bool thread_per_row(int64_t D, int64_t units, int64_t L, int64_t Lk) {
+  if (L > 64 || D >= 96) return false;
+  if (D < 16) return Lk <= (units >= 16384 ? 6 : units >= 8192 ? 4 : 0);
+  if (D < 32) return units >= 16384 && Lk <= 2;
+  return Lk <= (units >= 8192 ? 3 : units >= 4096 ? 2 : 0);
+}
 
 enum Which { FWD, DQ, DKV };
+
+template <int DP, int NW>
+void launch_mfma_fwd(const ParamsF& p, uint32_t blocks, hipStream_t s) {
+  hipLaunchKernelGGL((attn_f32_mfma_kernel<DP, NW>), dim3(blocks), dim3(64 * NW), 0, s, p);
+}
 
 template <int DP, int NW>
 void launch_mfma(Which which, const ParamsF& p, uint32_t blocks, hipStream_t s) {
   const dim3 g(blocks), b(64 * NW);
   if (which == FWD)
-    hipLaunchKernelGGL((attn_f32_mfma_kernel<DP, NW>), g, b, 0, s, p);
+    launch_mfma_fwd<DP, NW>(p, blocks, s);
   else if (which == DQ)
     hipLaunchKernelGGL((attn_bwd_f32_dq_mfma_kernel<DP, NW>), g, b, 0, s, p);
   else
@@ -531,24 +639,47 @@ void launch_mfma(Which which, const ParamsF& p, uint32_t blocks, hipStream_t s) 
 
 // One kernel over `units` units of `rows` owned rows each.
 int launch_units(Which which, ParamsF p, int64_t units, int64_t rows, hipStream_t s) {
-  const int nw = rows <= 32 ? 1 : 4;
+  if (which == FWD && wave_per_unit(p.D, units, p.L, p.Lk)) {
+    const int64_t most = grid_blocks(64);
+    for (p.first = 0; p.first < units; p.first += most) {
+      const dim3 g((uint32_t)std::min(most, units - p.first)), b(64);
+      switch (p.D) {
+        case 16: hipLaunchKernelGGL(attn_f32_unit_kernel<16>, g, b, 0, s, p); break;
+        case 32: hipLaunchKernelGGL(attn_f32_unit_kernel<32>, g, b, 0, s, p); break;
+        case 64: hipLaunchKernelGGL(attn_f32_unit_kernel<64>, g, b, 0, s, p); break;
+        case 72: hipLaunchKernelGGL(attn_f32_unit_kernel<72>, g, b, 0, s, p); break;
+        case 80: hipLaunchKernelGGL(attn_f32_unit_kernel<80>, g, b, 0, s, p); break;
+        default: hipLaunchKernelGGL(attn_f32_unit_kernel<96>, g, b, 0, s, p); break;
+      }
+      const int st = last_launch_status();
+      if (st != DSP_OK) return st;
+    }
+    return DSP_OK;
+  }
+  // 33 to 64 rows: two waves where there are enough units (D = 72, us with four / two waves:
+  // 8192 units of 33 rows 319 / 165, 1024 43 / 27, 64 12.3 / 12.9: few units gain from four
+  // waves fetching a tile).  In the gradients four hold fewer registers.
+  const int nw = rows <= 32 ? 1 : rows <= 64 && which == FWD && units >= 512 ? 2 : 4;
   const int64_t n_blk = (rows + 32 * nw - 1) / (32 * nw), most = grid_blocks(64 * nw) / n_blk;  // units of one grid
   const int dp = padded_width(p.D);
-  if (dp && most > 0) {
+  if (dp && most > 0 && !(which == FWD && thread_per_row(p.D, units, p.L, p.Lk))) {
     // one launch, or several where the threads are too many for a grid
     p.n_blk = (uint32_t)n_blk;
     for (p.first = 0; p.first < units; p.first += most) {
       const uint32_t n = (uint32_t)(std::min(most, units - p.first) * n_blk);
-#define DSP_F32_CASE(DP_)                                                                            \
-  case DP_:                                                                                          \
-    nw == 1 ? launch_mfma<DP_, 1>(which, p, n, s) : launch_mfma<DP_, 4>(which, p, n, s);             \
+#define DSP_F32_CASE(DP_)                                 \
+  case DP_:                                               \
+    nw == 1   ? launch_mfma<DP_, 1>(which, p, n, s)       \
+    : nw == 2 ? launch_mfma_fwd<DP_, 2>(p, n, s)          \
+              : launch_mfma<DP_, 4>(which, p, n, s);      \
     break
       switch (dp) {
+        DSP_F32_CASE(16);
         DSP_F32_CASE(32);
         DSP_F32_CASE(64);
         DSP_F32_CASE(72);
         DSP_F32_CASE(96);
-        default: nw == 1 ? launch_mfma<128, 1>(which, p, n, s) : launch_mfma<128, 4>(which, p, n, s);
+        DSP_F32_CASE(128);
       }
 #undef DSP_F32_CASE
       const int st = last_launch_status();
