@@ -277,6 +277,22 @@ __global__ __launch_bounds__(FTHR* KS) void gemm_f32_mfma_kernel(F32Gemm p) {
   }
 }
 
+// A gradient whose reduction is a few terms: one thread per output.  The tiles above work
+// through 32 terms whatever there are (dW of one row, 64 x 64: 4.4 against 5.7 us;
+// 1152 x 1152: 6.3 against 7.5, of 8 rows 8.9 against 7.5).
+template <bool TA>
+__global__ __launch_bounds__(256) void gemm_f32_few_terms_kernel(F32Gemm p) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x, N = (uint32_t)p.N;
+  if (i >= (uint32_t)(p.M * p.N)) return;
+  const uint32_t m = i / N, n = i - m * N;
+  float v = 0.0f;
+  for (int k = 0; k < (int)p.K; ++k) v = fmaf(p.a[TA ? k * p.lda + m : m * p.lda + k], p.b[k * p.ldb + n], v);
+  p.out[i] = f32_epilogue(p, v, i, i, n);
+}
+bool few_terms(int64_t M, int64_t N, int64_t K) {
+  return K <= 2 ? M * N < (int64_t(1) << 31) : K <= 16 && M * N <= 65536;
+}
+
 bool al16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 // Groups per tile: as many as keep the whole grid resident at once (256 CUs, at
@@ -367,6 +383,14 @@ int launch_gemm_grad_f32(const float* a, int ta, int64_t lda, const float* b, in
   p.N = N;
   p.K = K;
   if (!tb) return DSP_ERR_ARG;  // the gradients' layouts: B always has its reduction index strided
+  if (M > 0 && N > 0 && few_terms(M, N, K)) {
+    const dim3 grid((uint32_t)((M * N + 255) / 256));
+    if (ta)
+      hipLaunchKernelGGL(gemm_f32_few_terms_kernel<true>, grid, dim3(256), 0, s, p);
+    else
+      hipLaunchKernelGGL(gemm_f32_few_terms_kernel<false>, grid, dim3(256), 0, s, p);
+    return last_launch_status();
+  }
   return ta ? launch_f32<true, true>(p, s) : launch_f32<false, true>(p, s);
 }
 

@@ -12,7 +12,8 @@ from tests.gpu_util import say
 pytestmark = pytest.mark.gpu
 
 SIZES = [(1, 1, 1), (63, 65, 31), (64, 64, 32), (65, 66, 33), (129, 127, 36), (5, 1152, 72), (4100, 2052, 44),
-         (4097, 2049, 7), (70, 300, 1030), (600, 1300, 260), (100, 90, 2049)]
+         (4097, 2049, 7), (70, 300, 1030), (600, 1300, 260), (100, 90, 2049),
+         (2, 1160, 257), (3, 100, 37), (16, 200, 320), (17, 130, 70), (300, 2, 1152), (40, 16, 129), (33, 17, 900)]
 
 
 def _off(a, off):
