@@ -342,6 +342,32 @@ __global__ __launch_bounds__(CS_THREADS) void colsum_kernel(const void* __restri
   }
 }
 
+// A few rows: one thread per 16-byte chunk (bf16) or column (fp32).  The tree of a
+// 1024-thread work-group takes longer than the rows do (8 fp32 rows of 64 columns with
+// their weight gradient 6.6 against 7.8 us).
+constexpr int kFewRows = 16;
+template <bool BF>
+__global__ __launch_bounds__(256) void colsum_few_kernel(const void* __restrict__ dyp, float* db, int M, int N) {
+  constexpr int V = BF ? 8 : 1;
+  const int64_t n = ((int64_t)blockIdx.x * 256 + threadIdx.x) * V;
+  if (n >= N) return;
+  float s[V] = {};
+  for (int m = 0; m < M; ++m) {
+    if constexpr (BF) {  // N is a multiple of 8
+      const u32x4 w = *reinterpret_cast<const u32x4*>(static_cast<const bf16*>(dyp) + (int64_t)m * N + n);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s[2 * i] += __uint_as_float(w[i] << 16);
+        s[2 * i + 1] += __uint_as_float(w[i] & 0xFFFF0000u);
+      }
+    } else {
+      s[0] += static_cast<const float*>(dyp)[(int64_t)m * N + n];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < V; ++i) db[n + i] = s[i];
+}
+
 // ---------------------------------------------------------------------------
 // Weight gradient: out[M][N] = sum over k of a[k][m] b[k][n] (both operands stored
 // with the reduction index as rows: dW = dy^T x), fp32, the reduction split over
@@ -647,6 +673,11 @@ int launch_add_f32(const float* a, const float* b, float* out, int64_t n, hipStr
 // columns.
 int launch_colsum_f32(const float* dy, float* db, int64_t M, int N, hipStream_t s) {
   if (N == 0) return DSP_OK;
+  if (M <= kFewRows) {
+    hipLaunchKernelGGL(colsum_few_kernel<false>, dim3((uint32_t)(((int64_t)N + 255) / 256)), dim3(256), 0, s, dy, db,
+                       (int)M, N);
+    return last_launch_status();
+  }
   constexpr int G = 16;
   // one launch, or several where the threads are too many for a grid (2^26 columns)
   const int64_t groups = ((int64_t)N + G - 1) / G, most = grid_blocks(CS_THREADS);
@@ -722,6 +753,10 @@ int launch_gemm_grad(const void* a, int ta, int64_t lda, const void* b, int tb, 
 // CU one.
 int launch_colsum_bf16(const void* dy, float* db, int64_t M, int N, hipStream_t s) {
   if (N == 0) return DSP_OK;
+  if (M <= kFewRows) {
+    hipLaunchKernelGGL(colsum_few_kernel<true>, dim3((uint32_t)((N / 8 + 255) / 256)), dim3(256), 0, s, dy, db, (int)M, N);
+    return last_launch_status();
+  }
   if (N >= 128 * 32)
     hipLaunchKernelGGL((colsum_kernel<true, 4>), dim3((uint32_t)((N + 31) / 32)), dim3(CS_THREADS), 0, s, dy, db, M, N,
                        0);
