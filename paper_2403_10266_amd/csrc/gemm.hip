@@ -335,509 +335,27 @@ __global__ __launch_bounds__(NTHR, 2) void gemm_bf16_kernel(
   }
 }
 
-// Large-tile variant for problems with many tiles: 256 x (64 TN) output tile,
-// 4 waves of 128 x (32 TN), one work-group per CU (one wave per SIMD) with the
-// accumulators in AGPRs.  Two LDS buffers, so one barrier per 64-wide K slice;
-// the next slice's LDS stores, each followed by the global load that refills
-// its register, are spread between the MFMAs of the current slice's first
-// three steps, and each 16-wide K step's fragments are read from LDS during
-// the previous step's MFMAs.  The barrier sits before the slice's last step: by
-// then every wave has stored the next slice (steps 0-2) and read this slice's
-// last fragments, so the next slice's first fragments are read during the
-// last step's MFMAs instead of after a barrier at the slice's end.  The MFMAs
-// and their k order are those of gemm_bf16_kernel, so both kernels give the
-// same bits.
-#ifndef DSP_GEMM_BIG_GROUP
-#define DSP_GEMM_BIG_GROUP 4
-#endif
-constexpr int BIG_BM = 256, BIG_GROUP = DSP_GEMM_BIG_GROUP;
-
-template <int EPI, bool KEEP, int TN>
-__global__ __launch_bounds__(NTHR, 1) void gemm_bf16_big_kernel(
-    const bf16* __restrict__ A, const bf16* __restrict__ W, const bf16* __restrict__ bias,
-    const float* resid, void* out, bf16* keep_out, int M, int N, int K, int n_ntiles, int n_tiles,
-    RowSwap rs) {
-  constexpr int TM = 4;
-  constexpr int BNB = 2 * TN * 32;
-  constexpr int STAGE = (BIG_BM + BNB) * PITCH;
-  __shared__ __attribute__((aligned(16))) bf16 lds[2 * STAGE];
-
-  // tile order: contiguous ranges per XCD, then groups of BIG_GROUP m-tiles
-  // with m fastest, so that the A and W slices of the tiles running together
-  // on one XCD fit its L2
-  uint32_t bid = blockIdx.x;
-  if ((n_tiles & 7) == 0) bid = (bid & 7u) * ((uint32_t)n_tiles >> 3) + (bid >> 3);
-  const int n_mt = n_tiles / n_ntiles;
-  const int per_group = BIG_GROUP * n_ntiles;
-  const int grp = (int)bid / per_group;
-  const int first_m = grp * BIG_GROUP;
-  const int gm = min(BIG_GROUP, n_mt - first_m);
-  const int rem = (int)bid - grp * per_group;
-  const int m0 = (first_m + rem % gm) * BIG_BM, n0 = (rem / gm) * BNB;
-
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
-  const int l32 = lane & 31, g = lane >> 5;
-
-  // loader: thread t moves 16-byte chunk (row t/8 + 32 i, column 8 (t % 8))
-  constexpr int A_LOADS = BIG_BM / 32, W_LOADS = BNB / 32, NL = A_LOADS + W_LOADS;
-  const int lrow = threadIdx.x >> 3, lcol = threadIdx.x & 7;
-  const uint32_t row_bytes = (uint32_t)K * 2u;
-  const uint32_t a_rows = (uint32_t)min(BIG_BM, M - m0), w_rows = (uint32_t)min(BNB, N - n0);
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc(A + (int64_t)m0 * K, a_rows * row_bytes);
-  const __amdgpu_buffer_rsrc_t rw = make_rsrc(W + (int64_t)n0 * K, w_rows * row_bytes);
-  const uint32_t off0 = (uint32_t)lrow * row_bytes + (uint32_t)lcol * 16u;
-  const uint32_t step32 = 32u * row_bytes;
-  u32x4 pre[NL];
-  auto gload = [&](int i, int k0) {
-    // columns past K: an offset past every range reads zero
-    const bool kin = k0 + 8 * lcol < K;
-    const uint32_t off = off0 + (uint32_t)k0 * 2u;
-    if (i < A_LOADS)
-      pre[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, kin ? off + i * step32 : 0xFFFFFFF0u, 0, 0);
-    else
-      pre[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, kin ? off + (i - A_LOADS) * step32 : 0xFFFFFFF0u, 0, 0);
-  };
-  auto lstore = [&](int i, int buf) {
-    bf16* As = lds + buf * STAGE;
-    bf16* Ws = As + BIG_BM * PITCH;
-    if (i < A_LOADS)
-      *reinterpret_cast<u32x4*>(As + (lrow + 32 * i) * PITCH + lcol * 8) = pre[i];
-    else
-      *reinterpret_cast<u32x4*>(Ws + (lrow + 32 * (i - A_LOADS)) * PITCH + lcol * 8) = pre[i];
-  };
-
-  floatx16 acc[TN][TM];
-#pragma unroll
-  for (int a = 0; a < TN; ++a)
-#pragma unroll
-    for (int b = 0; b < TM; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-  bf16x8 af[2][TM], wf[2][TN];
-  auto fread = [&](int slot, int buf, int ks) {
-    const bf16* As = lds + buf * STAGE;
-    const bf16* Ws = As + BIG_BM * PITCH;
-#pragma unroll
-    for (int b = 0; b < TM; ++b)
-      af[slot][b] = *reinterpret_cast<const bf16x8*>(As + (wm * TM * 32 + 32 * b + l32) * PITCH + 16 * ks + 8 * g);
-#pragma unroll
-    for (int a = 0; a < TN; ++a)
-      wf[slot][a] = *reinterpret_cast<const bf16x8*>(Ws + (wn * TN * 32 + 32 * a + l32) * PITCH + 16 * ks + 8 * g);
-  };
-
-  // One K slice from LDS buffer kt & 1.  ST: store the prefetched slice kt + 1
-  // into the other buffer; LD: reload each prefetch register with its part of
-  // slice kt + 2 right after its store, which gives the loads a slice of MFMAs
-  // before their store.  The stores are spread over the MFMAs of the first
-  // three steps: in one step, they and the next step's fragment reads
-  // together needed more LDS bandwidth than the CU has (~190 of 128 B/clk).
-  auto slice = [&](int kt, auto st_c, auto ld_c) {
-    constexpr bool ST = decltype(st_c)::value, LD = decltype(ld_c)::value;
-    constexpr int NMF = TM * TN;
-    constexpr int NSPREAD = 3;  // steps that carry the next slice's LDS stores
-    const int b = kt & 1;
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const int cur = ks & 1;
-      if (ks + 1 < BK / 16) {
-        fread(cur ^ 1, b, ks + 1);
-      } else if (ST) {
-        __syncthreads();
-        fread(cur ^ 1, b ^ 1, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < NMF; ++j) {
-        const int a = j / TM, bb = j % TM;
-        acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[cur][a], af[cur][bb], acc[a][bb], 0, 0, 0);
-        if (ks < NSPREAD && ST) {
-#pragma unroll
-          for (int i = (ks * NMF + j) * NL / (NSPREAD * NMF); i < (ks * NMF + j + 1) * NL / (NSPREAD * NMF); ++i) {
-            lstore(i, b ^ 1);
-            if (LD) gload(i, (kt + 2) * BK);
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
-
-  const int nk = (K + BK - 1) / BK;
-#pragma unroll
-  for (int i = 0; i < NL; ++i) gload(i, 0);
-#pragma unroll
-  for (int i = 0; i < NL; ++i) lstore(i, 0);
-  if (nk > 1) {
-#pragma unroll
-    for (int i = 0; i < NL; ++i) gload(i, BK);
-  }
-  __syncthreads();
-  fread(0, 0, 0);
-  using yes = std::true_type;
-  using no = std::false_type;
-  int kt = 0;
-  for (; kt + 2 < nk; ++kt) slice(kt, yes{}, yes{});
-  if (kt + 1 < nk) {
-    slice(kt, yes{}, no{});
-    ++kt;
-  }
-  // Epilogue layout of the fp32-staged results (fp32 output, backward
-  // epilogues, pre-activation copy): NP passes of RPP rows (pass p: rows
-  // HR p + [0, HR) of each wave row half), 16-byte chunks of 4 columns, PER
-  // chunks per thread and pass.  Four passes where two would hold more
-  // residual or pre-activation reads than the registers do.
-  constexpr bool BWD = epi_is_bwd<EPI>();
-  constexpr bool F32OUT = EPI == DSP_EPI_RESID || EPI == DSP_EPI_F32;
-  constexpr int NP = (TN == 4 && (EPI == DSP_EPI_RESID || BWD)) ? 4 : 2;
-  constexpr int RPP = BIG_BM / NP, HR = RPP / 2, BPP = TM / NP;
-  constexpr int CPR4 = BNB / 4;
-  constexpr int PER = RPP * CPR4 / NTHR;
-  const uint32_t rrow = (uint32_t)N * 4u, urow = (uint32_t)N * 2u;
-  __amdgpu_buffer_rsrc_t rr, ru;
-  if constexpr (EPI == DSP_EPI_RESID) rr = make_rsrc(resid + (int64_t)m0 * N, a_rows * rrow);
-  if constexpr (BWD) ru = make_rsrc(keep_out + (int64_t)m0 * N, a_rows * urow);
-  constexpr int NRV = EPI == DSP_EPI_RESID ? PER : 1, NUV = BWD ? PER : 1;
-  // the residual or saved pre-activation chunks of pass p
-  auto side_loads = [&](int p, u32x4 (&rv)[NRV], u32x2 (&uv)[NUV]) {
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int c = (int)threadIdx.x + NTHR * q;
-      const int sr = c / CPR4, cc = c % CPR4;
-      const uint32_t tr = (uint32_t)((sr / HR) * 128 + HR * p + sr % HR);
-      const int n = n0 + 4 * cc;
-      if constexpr (EPI == DSP_EPI_RESID)
-        rv[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, n < N ? tr * rrow + (uint32_t)n * 4u : 0xFFFFFFF0u, 0, 0);
-      if constexpr (BWD)
-        uv[q] = __builtin_amdgcn_raw_buffer_load_b64(ru, n < N ? tr * urow + (uint32_t)n * 2u : 0xFFFFFFF0u, 0, 0);
-    }
-  };
-  // the first pass's reads go out before the last slice, whose MFMAs then
-  // hide their latency
-  u32x4 rv0[NRV];
-  u32x2 uv0[NUV];
-  if constexpr (EPI == DSP_EPI_RESID || BWD) side_loads(0, rv0, uv0);
-  slice(kt, no{}, no{});
-
-  // Epilogue (N is a multiple of 8 here).  The accumulators hold, per lane,
-  // rows m = .. + 32 bb + l32 and in each the column groups
-  // n = .. + 32 a + 8 r4 + 4 g + {0..3}: stored from there, one store
-  // instruction would write 16-byte pieces of 32 rows, and the L2 would take
-  // a request per piece.  So the tile goes through LDS (free once every wave
-  // has read its last fragments) and leaves in whole rows: 64 lanes write
-  // consecutive 16-byte chunks of one or two rows.
-  constexpr int NG = TN * 4;  // column groups of 4 per lane and row
-  // Bias of each column group, kept as bf16 pairs until used.  Without a
-  // bias the loads read nothing (empty range) and the pairs become -0, the
-  // one addend that leaves every value, -0 included, unchanged: the adds stay
-  // unconditional, with no branch for the accumulators to be copied across.
-  u32x2 braw[NG];
-  {
-    const __amdgpu_buffer_rsrc_t rb = make_rsrc(bias, bias ? (uint32_t)N * 2u : 0u);
-    const uint32_t neg0 = bias ? 0u : 0x80008000u;
-#pragma unroll
-    for (int j = 0; j < NG; ++j) {
-      const int n = n0 + wn * TN * 32 + 32 * (j / 4) + 8 * (j % 4) + 4 * g;
-      braw[j] = __builtin_amdgcn_raw_buffer_load_b64(rb, n < N ? (uint32_t)n * 2u : 0xFFFFFFF0u, 0, 0);
-      braw[j][0] |= neg0;
-      braw[j][1] |= neg0;
-    }
-  }
-  // a W + bias of accumulator row block bb, column group j
-  auto sum4 = [&](int bb, int j, float v[4]) {
-    const int a = j / 4, r4 = j % 4;
-    v[0] = acc[a][bb][4 * r4 + 0] + __uint_as_float(braw[j][0] << 16);
-    v[1] = acc[a][bb][4 * r4 + 1] + __uint_as_float(braw[j][0] & 0xFFFF0000u);
-    v[2] = acc[a][bb][4 * r4 + 2] + __uint_as_float(braw[j][1] << 16);
-    v[3] = acc[a][bb][4 * r4 + 3] + __uint_as_float(braw[j][1] & 0xFFFF0000u);
-  };
-  // output row of each tile row (the row swap evaluated once per row), at
-  // the end of the LDS buffers, past every staged row
-  uint32_t* orows = reinterpret_cast<uint32_t*>(lds + 2 * STAGE) - BIG_BM;
-  auto put_orow = [&]() {
-    const int m = m0 + (int)threadIdx.x;
-    orows[threadIdx.x] = (uint32_t)rs.map(m < M ? m : 0);
-  };
-  if constexpr (!F32OUT && !BWD) {
-    // bf16 results, activation applied in registers, staged as bf16 and
-    // stored in 16-byte chunks of 8 columns.  Two halves (accumulator row
-    // blocks 0-1, then 2-3, i.e. tile rows 64 h + [0, 64) of each wave row
-    // half): the first half's stores are in flight while the second half's
-    // activation is computed.  KEEP: the pre-activation copy of a half is
-    // staged in the other half's rows (tile row r ^ 64), free at that time.
-    constexpr int SP = BNB + 8;  // staged row pitch (bf16): a 16-byte pad
-    static_assert(BIG_BM * SP * 2 + BIG_BM * 4 <= 2 * STAGE * 2, "bf16 staging fits the LDS buffers");
-    constexpr int CPR = BNB / 8;  // chunks per row
-    bf16* st = lds;
-    __syncthreads();
-    put_orow();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if (KEEP && h == 1) __syncthreads();  // the first half's copies are read
-#pragma unroll
-      for (int bb = 2 * h; bb < 2 * h + 2; ++bb)
-#pragma unroll
-        for (int j = 0; j < NG; ++j) {
-          float v[4];
-          sum4(bb, j, v);
-          const int col = wn * TN * 32 + 32 * (j / 4) + 8 * (j % 4) + 4 * g;
-          const int row = wm * TM * 32 + 32 * bb + l32;
-          if (KEEP) {
-            float k[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) k[i] = kept<EPI>(v[i]);
-            *reinterpret_cast<uint2*>(st + (row ^ 64) * SP + col) = pack_bf16x4(k);
-          }
-          if (epi_is_gelu<EPI>()) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = gelu_bf16out(v[i]);
-          }
-          if (EPI == DSP_EPI_RELU) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.0f);
-          }
-          *reinterpret_cast<uint2*>(st + row * SP + col) = pack_bf16x4(v);
-        }
-      __syncthreads();
-#pragma unroll 4
-      for (int q = 0; q < CPR / 2; ++q) {
-        const int c = (int)threadIdx.x + NTHR * q;
-        const int sr = c / CPR, cc = c % CPR;
-        const int tr = (sr / 64) * 128 + 64 * h + sr % 64;
-        const int m = m0 + tr, n = n0 + 8 * cc;
-        const u32x4 w = *reinterpret_cast<const u32x4*>(st + tr * SP + 8 * cc);
-        const int64_t o = (int64_t)orows[tr] * N + n;
-        if (m < M && n < N) {
-          *reinterpret_cast<u32x4*>(static_cast<bf16*>(out) + o) = w;
-          if (KEEP)
-            *reinterpret_cast<u32x4*>(keep_out + o) = *reinterpret_cast<const u32x4*>(st + (tr ^ 64) * SP + 8 * cc);
-        }
-      }
-    }
-  } else {
-    // fp32 staging: the reads of pass p > 0 are issued before its staging
-    constexpr int SPF = BNB + 4;  // staged row pitch (fp32): a 16-byte pad
-    static_assert(RPP * SPF * 4 + BIG_BM * 4 <= 2 * STAGE * 2, "fp32 staging fits the LDS buffers");
-    constexpr int CPR = CPR4;
-    float* sf = reinterpret_cast<float*>(lds);
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      u32x4 rv[NRV];
-      u32x2 uv[NUV];
-      if (p == 0) {
-#pragma unroll
-        for (int q = 0; q < NRV; ++q) rv[q] = rv0[q];
-#pragma unroll
-        for (int q = 0; q < NUV; ++q) uv[q] = uv0[q];
-      } else if constexpr (EPI == DSP_EPI_RESID || BWD) {
-        side_loads(p, rv, uv);
-      }
-      __syncthreads();  // p = 0: last fragments read; p > 0: the previous pass's rows read
-      if (p == 0) put_orow();
-#pragma unroll
-      for (int h = 0; h < BPP; ++h)
-#pragma unroll
-        for (int j = 0; j < NG; ++j) {
-          float v[4];
-          sum4(BPP * p + h, j, v);
-          const int col = wn * TN * 32 + 32 * (j / 4) + 8 * (j % 4) + 4 * g;
-          *reinterpret_cast<float4*>(sf + (wm * HR + 32 * h + l32) * SPF + col) = make_float4(v[0], v[1], v[2], v[3]);
-        }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int c = (int)threadIdx.x + NTHR * q;
-        const int sr = c / CPR, cc = c % CPR;
-        const int tr = (sr / HR) * 128 + HR * p + sr % HR;
-        const int m = m0 + tr, n = n0 + 4 * cc;
-        const float4 s4 = *reinterpret_cast<const float4*>(sf + sr * SPF + 4 * cc);
-        if (m >= M || n >= N) continue;
-        float v[4] = {s4.x, s4.y, s4.z, s4.w};
-        const int64_t orow = (int64_t)orows[tr] * N;
-        if (KEEP) {
-          float k[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) k[i] = kept<EPI>(v[i]);
-          *reinterpret_cast<uint2*>(keep_out + orow + n) = pack_bf16x4(k);
-        }
-        if constexpr (BWD) {
-          const uint32_t w0 = uv[q][0], w1 = uv[q][1];
-          v[0] *= act_grad<EPI>(__uint_as_float(w0 << 16));
-          v[1] *= act_grad<EPI>(__uint_as_float(w0 & 0xFFFF0000u));
-          v[2] *= act_grad<EPI>(__uint_as_float(w1 << 16));
-          v[3] *= act_grad<EPI>(__uint_as_float(w1 & 0xFFFF0000u));
-        }
-        if (epi_is_gelu<EPI>()) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = gelu_bf16out(v[i]);
-        }
-        if (EPI == DSP_EPI_RELU) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.0f);
-        }
-        if constexpr (EPI == DSP_EPI_RESID) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] += __uint_as_float(rv[q][i]);
-        }
-        if (F32OUT)
-          *reinterpret_cast<float4*>(static_cast<float*>(out) + orow + n) = make_float4(v[0], v[1], v[2], v[3]);
-        else
-          *reinterpret_cast<uint2*>(static_cast<bf16*>(out) + orow + n) = pack_bf16x4(v);
-      }
-    }
-  }
+// LDS elements the epilogue of a 64 TM x 64 TN tile stages its rows in.
+template <int EPI, bool KEEP, int TM, int TN>
+constexpr int epilogue_elems() {
+  constexpr int BMT = 64 * TM, BNB = 64 * TN;
+  if (epi_is_bwd<EPI>() || EPI == DSP_EPI_RESID || EPI == DSP_EPI_F32)
+    return BMT / (TM == 4 && TN == 4 && EPI != DSP_EPI_F32 ? 4 : TM >= 2 ? 2 : 1) * (BNB + 4) * 2 + 2 * BMT;
+  return BMT * (BNB + 8) * (KEEP && TM == 1 ? 2 : 1) + 2 * BMT;
 }
 
-// Tiles of 64 TM x 64 TN (4 waves of 32 TM x 32 TN), K a multiple of 64: slices of
-// both operands go from memory straight into a ring of NS LDS buffers, up to NS
-// slices in flight, and OCC work-groups share a CU, so one's epilogue and
-// barriers run under the other's MFMAs.  It needs no registers for the loads.
-// Bound by LDS bandwidth once the chip is full (128 x 192 tiles: 2.5 KB of
-// fragments and 1.25 KB of loads per 12 MFMAs and wave, of 128 bytes a clock), and
-// by the length of the K loop when it is not, which smaller tiles shorten: one
-// 64-wide slice takes 0.23 us on 64 x 64 tiles, 0.50 on 64 x 128, 0.59 on 128 x 128,
-// 0.68 on 128 x 192 with a work-group per CU.  The schedule inside a slice, the MFMAs
-// and their k order are those of gemm_bf16_big_kernel: the same bits.
-//   1200 x 4608 x 1152 + GELU 46 -> 21 us, 300 x 1152 x 1152 + residual 38 -> 7.6,
-// 2500 x 1152 x 4608 106 -> 51, 13600 x 1152 x 1152 65 -> 48 (256 x 128 or 256 x 192
-// tiles before).  Slices of 32 (256 x 128 and 128 x 256 tiles, two work-groups per
-// CU): 284 us against 239 for 128 x 192 tiles and 64-wide slices at 32768 x 3456 x 1152.
-template <int EPI, bool KEEP, int TM, int TN, int NS, int OCC>
-__global__ __launch_bounds__(NTHR, OCC) void gemm_bf16_dma_kernel(
-    const bf16* __restrict__ A, const bf16* __restrict__ W, const bf16* __restrict__ bias,
-    const float* resid, void* out, bf16* keep_out, int M, int N, int K, int n_ntiles, int n_tiles,
-    RowSwap rs) {
+// Epilogue of a work-group's 64 TM x 64 TN tile (4 waves of 32 TM x 32 TN, N a multiple
+// of 8), from the accumulators through LDS, which holds LDS_ELEMS elements, to memory.
+// `last_slice` multiplies the last K slice: what the epilogue reads is asked for before it.
+template <int EPI, bool KEEP, int TM, int TN, int LDS_ELEMS, typename LastSlice>
+__device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[TN][TM], bf16* lds, const bf16* __restrict__ bias,
+                                              const float* resid, void* out, bf16* keep_out, int M, int N, int m0,
+                                              int n0, const RowSwap& rs, LastSlice last_slice) {
   constexpr int BMT = 64 * TM, BNB = 64 * TN;
-  constexpr int STAGE = (BMT + BNB) * BK;  // elements of one K slice of both operands
-  // the slices' buffers, and after them the epilogue's staged rows
-  constexpr int EPI_BF16 = BMT * (BNB + 8) * (KEEP && TM == 1 ? 2 : 1) + 2 * BMT;
-  constexpr int EPI_F32 = BMT / (TM == 4 && TN == 4 && EPI != DSP_EPI_F32 ? 4 : TM >= 2 ? 2 : 1) * (BNB + 4) * 2 + 2 * BMT;
-  constexpr int EPI_ELEMS = epi_is_bwd<EPI>() || EPI == DSP_EPI_RESID || EPI == DSP_EPI_F32 ? EPI_F32 : EPI_BF16;
-  constexpr int LDS_ELEMS = NS * STAGE > EPI_ELEMS ? NS * STAGE : EPI_ELEMS;
-  __shared__ __attribute__((aligned(1024))) bf16 lds[LDS_ELEMS];
-
-  // tile order: contiguous ranges per XCD, then groups of BIG_GROUP m-tiles
-  // with m fastest, so that the A and W slices of the tiles running together
-  // on one XCD fit its L2
-  uint32_t bid = blockIdx.x;
-  {
-    const uint32_t per = (uint32_t)n_tiles >> 3, extra = (uint32_t)n_tiles & 7u, xcd = bid & 7u;
-    bid = xcd * per + min(xcd, extra) + (bid >> 3);
-  }
-  const int n_mt = n_tiles / n_ntiles;
-  constexpr int GROUP = BIG_GROUP * 256 / BMT;  // m-tiles of 1024 rows
-  const int per_group = GROUP * n_ntiles;
-  const int grp = (int)bid / per_group;
-  const int first_m = grp * GROUP;
-  const int gm = min(GROUP, n_mt - first_m);
-  const int rem = (int)bid - grp * per_group;
-  const int m0 = (first_m + rem % gm) * BMT, n0 = (rem / gm) * BNB;
-
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave & 1, wn = wave >> 1;
   const int l32 = lane & 31, g = lane >> 5;
-
-  // Loader: one instruction moves 64 16-byte chunks (8 rows of a slice) straight
-  // into LDS, lane after lane.  Rows lie unpadded (128 bytes); lane (r, p) of a
-  // group of 8 rows fetches logical chunk p ^ r, so that a column of chunks is
-  // spread over all banks when fragments read it.  Rows past the end re-read the
-  // last one: they only enter outputs that are not stored.
-  constexpr int A_LOADS = BMT / 32, W_LOADS = BNB / 32, NL = A_LOADS + W_LOADS;
-  const uint32_t row_bytes = (uint32_t)K * 2u;
-  const int a_rows = min(BMT, M - m0), w_rows = min(BNB, N - n0);
-  const u32x4 ra = dma_rsrc(A + (int64_t)m0 * K, (uint32_t)a_rows * row_bytes);
-  const u32x4 rw = dma_rsrc(W + (int64_t)n0 * K, (uint32_t)w_rows * row_bytes);
-  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16*)lds + (uint32_t)wave * 1024u);
-  uint32_t goff[NL];
-  {
-    const int r = lane >> 3, ch = (lane & 7) ^ r;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int row = 8 * (wave + 4 * (i < A_LOADS ? i : i - A_LOADS)) + r;
-      goff[i] = (uint32_t)min(row, (i < A_LOADS ? a_rows : w_rows) - 1) * row_bytes + (uint32_t)ch * 16u;
-    }
-  }
-  // load i of slice kt into LDS buffer buf
-  auto dma = [&](int i, int kt, int buf) {
-    const uint32_t at = lds0 + (uint32_t)buf * (STAGE * 2) + (i < A_LOADS ? i * 4096 : BMT * BK * 2 + (i - A_LOADS) * 4096);
-    dma_b128(i < A_LOADS ? ra : rw, goff[i], (uint32_t)kt * (BK * 2), at);
-  };
-
-  floatx16 acc[TN][TM];
-#pragma unroll
-  for (int a = 0; a < TN; ++a)
-#pragma unroll
-    for (int b = 0; b < TM; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-  bf16x8 af[2][TM], wf[2][TN];
-  auto fread = [&](int slot, int buf, int ks) {
-    const bf16* As = lds + buf * STAGE + l32 * BK + (((2 * ks + g) ^ (l32 & 7)) * 8);
-    const bf16* Ws = As + BMT * BK;
-#pragma unroll
-    for (int b = 0; b < TM; ++b) af[slot][b] = *reinterpret_cast<const bf16x8*>(As + (wm * TM + b) * 32 * BK);
-#pragma unroll
-    for (int a = 0; a < TN; ++a) wf[slot][a] = *reinterpret_cast<const bf16x8*>(Ws + (wn * TN + a) * 32 * BK);
-  };
-
-  // One K slice from LDS buffer `buf`.  MORE: slice kt + 1 exists; before the last
-  // 16-wide step the wave waits until its loads of that slice have landed
-  // (LEFT slices after it may still be in flight) and until its own fragment
-  // reads of this slice have returned; behind the barrier the next slice is
-  // whole and this one's buffer is free.  LD: slice kt + NS goes there.
-  auto slice = [&](int kt, int buf, auto more_c, auto left_c, auto ld_c) {
-    constexpr bool MORE = decltype(more_c)::value, LD = decltype(ld_c)::value;
-    constexpr int LEFT = decltype(left_c)::value, NMF = TM * TN;
-    const int nbuf = buf + 1 == NS ? 0 : buf + 1;
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const int cur = ks & 1;
-      if (ks + 1 < BK / 16) {
-        fread(cur ^ 1, buf, ks + 1);
-      } else if (MORE) {
-        wait_barrier<LEFT * NL>();
-        fread(cur ^ 1, nbuf, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < NMF; ++j) {
-        const int a = j / TM, bb = j % TM;
-        acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[cur][a], af[cur][bb], acc[a][bb], 0, 0, 0);
-        if (LD && ks + 1 == BK / 16) {
-#pragma unroll
-          for (int i = j * NL / NMF; i < (j + 1) * NL / NMF; ++i) dma(i, kt + NS, buf);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
-
-  const int nk = K / BK;
-  for (int t = 0; t < min(NS, nk); ++t)
-#pragma unroll
-    for (int i = 0; i < NL; ++i) dma(i, t, t);
-  // slice 0 landed: at most min(NS, nk) - 1 later ones in flight
-  if (nk >= NS)
-    wait_barrier<(NS - 1) * NL>();
-  else
-    wait_barrier<0>();
-  fread(0, 0, 0);
-  using yes = std::true_type;
-  using no = std::false_type;
-  int kt = 0, buf = 0;
-  for (; kt + NS < nk; ++kt) {
-    slice(kt, buf, yes{}, std::integral_constant<int, NS - 2>{}, yes{});
-    buf = buf + 1 == NS ? 0 : buf + 1;
-  }
-  // the last NS slices: nothing more to load (and all of it was issued NS - 1
-  // slices ago: no need to count)
-  for (; kt + 1 < nk; ++kt) {
-    slice(kt, buf, yes{}, std::integral_constant<int, 0>{}, no{});
-    buf = buf + 1 == NS ? 0 : buf + 1;
-  }
+  const uint32_t a_rows = (uint32_t)min(BMT, M - m0);
   // Epilogue layout of the fp32-staged results (fp32 output, backward
   // epilogues, pre-activation copy): NP passes of RPP rows (pass p: rows
   // HR p + [0, HR) of each wave row half), 16-byte chunks of 4 columns, PER
@@ -845,7 +363,7 @@ __global__ __launch_bounds__(NTHR, OCC) void gemm_bf16_dma_kernel(
   // residual or pre-activation reads than the registers do.
   constexpr bool BWD = epi_is_bwd<EPI>();
   constexpr bool F32OUT = EPI == DSP_EPI_RESID || EPI == DSP_EPI_F32;
-  constexpr int NP = (TM == 4 && TN == 4 && (EPI == DSP_EPI_RESID || BWD)) ? 4 : TM >= 2 ? 2 : 1;
+  constexpr int NP = (TM == 4 && (EPI == DSP_EPI_RESID || (TN == 4 && BWD))) ? 4 : TM >= 2 ? 2 : 1;
   constexpr int RPP = BMT / NP, HR = RPP / 2, BPP = TM / NP;
   constexpr int CPR4 = BNB / 4;
   constexpr int PER = RPP * CPR4 / NTHR;
@@ -873,7 +391,7 @@ __global__ __launch_bounds__(NTHR, OCC) void gemm_bf16_dma_kernel(
   u32x4 rv0[NRV];
   u32x2 uv0[NUV];
   if constexpr (EPI == DSP_EPI_RESID || BWD) side_loads(0, rv0, uv0);
-  slice(kt, buf, no{}, std::integral_constant<int, 0>{}, no{});
+  last_slice();
 
   // Epilogue (N is a multiple of 8 here).  The accumulators hold, per lane,
   // rows m = .. + 32 bb + l32 and in each the column groups
@@ -1046,6 +564,310 @@ __global__ __launch_bounds__(NTHR, OCC) void gemm_bf16_dma_kernel(
       }
     }
   }
+}
+
+// Large-tile variant for problems with many tiles: 256 x (64 TN) output tile,
+// 4 waves of 128 x (32 TN), one work-group per CU (one wave per SIMD) with the
+// accumulators in AGPRs.  Two LDS buffers, so one barrier per 64-wide K slice;
+// the next slice's LDS stores, each followed by the global load that refills
+// its register, are spread between the MFMAs of the current slice's first
+// three steps, and each 16-wide K step's fragments are read from LDS during
+// the previous step's MFMAs.  The barrier sits before the slice's last step: by
+// then every wave has stored the next slice (steps 0-2) and read this slice's
+// last fragments, so the next slice's first fragments are read during the
+// last step's MFMAs instead of after a barrier at the slice's end.  The MFMAs
+// and their k order are those of gemm_bf16_kernel, so both kernels give the
+// same bits.
+#ifndef DSP_GEMM_BIG_GROUP
+#define DSP_GEMM_BIG_GROUP 4
+#endif
+constexpr int BIG_BM = 256, BIG_GROUP = DSP_GEMM_BIG_GROUP;
+
+template <int EPI, bool KEEP, int TN>
+__global__ __launch_bounds__(NTHR, 1) void gemm_bf16_big_kernel(
+    const bf16* __restrict__ A, const bf16* __restrict__ W, const bf16* __restrict__ bias,
+    const float* resid, void* out, bf16* keep_out, int M, int N, int K, int n_ntiles, int n_tiles,
+    RowSwap rs) {
+  constexpr int TM = 4;
+  constexpr int BNB = 2 * TN * 32;
+  constexpr int STAGE = (BIG_BM + BNB) * PITCH;
+  __shared__ __attribute__((aligned(16))) bf16 lds[2 * STAGE];
+
+  // tile order: contiguous ranges per XCD, then groups of BIG_GROUP m-tiles
+  // with m fastest, so that the A and W slices of the tiles running together
+  // on one XCD fit its L2
+  uint32_t bid = blockIdx.x;
+  if ((n_tiles & 7) == 0) bid = (bid & 7u) * ((uint32_t)n_tiles >> 3) + (bid >> 3);
+  const int n_mt = n_tiles / n_ntiles;
+  const int per_group = BIG_GROUP * n_ntiles;
+  const int grp = (int)bid / per_group;
+  const int first_m = grp * BIG_GROUP;
+  const int gm = min(BIG_GROUP, n_mt - first_m);
+  const int rem = (int)bid - grp * per_group;
+  const int m0 = (first_m + rem % gm) * BIG_BM, n0 = (rem / gm) * BNB;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int l32 = lane & 31, g = lane >> 5;
+
+  // loader: thread t moves 16-byte chunk (row t/8 + 32 i, column 8 (t % 8))
+  constexpr int A_LOADS = BIG_BM / 32, W_LOADS = BNB / 32, NL = A_LOADS + W_LOADS;
+  const int lrow = threadIdx.x >> 3, lcol = threadIdx.x & 7;
+  const uint32_t row_bytes = (uint32_t)K * 2u;
+  const uint32_t a_rows = (uint32_t)min(BIG_BM, M - m0), w_rows = (uint32_t)min(BNB, N - n0);
+  const __amdgpu_buffer_rsrc_t ra = make_rsrc(A + (int64_t)m0 * K, a_rows * row_bytes);
+  const __amdgpu_buffer_rsrc_t rw = make_rsrc(W + (int64_t)n0 * K, w_rows * row_bytes);
+  const uint32_t off0 = (uint32_t)lrow * row_bytes + (uint32_t)lcol * 16u;
+  const uint32_t step32 = 32u * row_bytes;
+  u32x4 pre[NL];
+  auto gload = [&](int i, int k0) {
+    // columns past K: an offset past every range reads zero
+    const bool kin = k0 + 8 * lcol < K;
+    const uint32_t off = off0 + (uint32_t)k0 * 2u;
+    if (i < A_LOADS)
+      pre[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, kin ? off + i * step32 : 0xFFFFFFF0u, 0, 0);
+    else
+      pre[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, kin ? off + (i - A_LOADS) * step32 : 0xFFFFFFF0u, 0, 0);
+  };
+  auto lstore = [&](int i, int buf) {
+    bf16* As = lds + buf * STAGE;
+    bf16* Ws = As + BIG_BM * PITCH;
+    if (i < A_LOADS)
+      *reinterpret_cast<u32x4*>(As + (lrow + 32 * i) * PITCH + lcol * 8) = pre[i];
+    else
+      *reinterpret_cast<u32x4*>(Ws + (lrow + 32 * (i - A_LOADS)) * PITCH + lcol * 8) = pre[i];
+  };
+
+  floatx16 acc[TN][TM];
+#pragma unroll
+  for (int a = 0; a < TN; ++a)
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+  bf16x8 af[2][TM], wf[2][TN];
+  auto fread = [&](int slot, int buf, int ks) {
+    const bf16* As = lds + buf * STAGE;
+    const bf16* Ws = As + BIG_BM * PITCH;
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+      af[slot][b] = *reinterpret_cast<const bf16x8*>(As + (wm * TM * 32 + 32 * b + l32) * PITCH + 16 * ks + 8 * g);
+#pragma unroll
+    for (int a = 0; a < TN; ++a)
+      wf[slot][a] = *reinterpret_cast<const bf16x8*>(Ws + (wn * TN * 32 + 32 * a + l32) * PITCH + 16 * ks + 8 * g);
+  };
+
+  // One K slice from LDS buffer kt & 1.  ST: store the prefetched slice kt + 1
+  // into the other buffer; LD: reload each prefetch register with its part of
+  // slice kt + 2 right after its store, which gives the loads a slice of MFMAs
+  // before their store.  The stores are spread over the MFMAs of the first
+  // three steps: in one step, they and the next step's fragment reads
+  // together needed more LDS bandwidth than the CU has (~190 of 128 B/clk).
+  auto slice = [&](int kt, auto st_c, auto ld_c) {
+    constexpr bool ST = decltype(st_c)::value, LD = decltype(ld_c)::value;
+    constexpr int NMF = TM * TN;
+    constexpr int NSPREAD = 3;  // steps that carry the next slice's LDS stores
+    const int b = kt & 1;
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      const int cur = ks & 1;
+      if (ks + 1 < BK / 16) {
+        fread(cur ^ 1, b, ks + 1);
+      } else if (ST) {
+        __syncthreads();
+        fread(cur ^ 1, b ^ 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < NMF; ++j) {
+        const int a = j / TM, bb = j % TM;
+        acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[cur][a], af[cur][bb], acc[a][bb], 0, 0, 0);
+        if (ks < NSPREAD && ST) {
+#pragma unroll
+          for (int i = (ks * NMF + j) * NL / (NSPREAD * NMF); i < (ks * NMF + j + 1) * NL / (NSPREAD * NMF); ++i) {
+            lstore(i, b ^ 1);
+            if (LD) gload(i, (kt + 2) * BK);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+
+  const int nk = (K + BK - 1) / BK;
+#pragma unroll
+  for (int i = 0; i < NL; ++i) gload(i, 0);
+#pragma unroll
+  for (int i = 0; i < NL; ++i) lstore(i, 0);
+  if (nk > 1) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) gload(i, BK);
+  }
+  __syncthreads();
+  fread(0, 0, 0);
+  using yes = std::true_type;
+  using no = std::false_type;
+  int kt = 0;
+  for (; kt + 2 < nk; ++kt) slice(kt, yes{}, yes{});
+  if (kt + 1 < nk) {
+    slice(kt, yes{}, no{});
+    ++kt;
+  }
+  tile_epilogue<EPI, KEEP, TM, TN, 2 * STAGE>(acc, lds, bias, resid, out, keep_out, M, N, m0, n0, rs,
+                                              [&] { slice(kt, no{}, no{}); });
+}
+
+// Tiles of 64 TM x 64 TN (4 waves of 32 TM x 32 TN), K a multiple of 64: slices of
+// both operands go from memory straight into a ring of NS LDS buffers, up to NS
+// slices in flight, and OCC work-groups share a CU, so one's epilogue and
+// barriers run under the other's MFMAs.  It needs no registers for the loads.
+// Bound by LDS bandwidth once the chip is full (128 x 192 tiles: 2.5 KB of
+// fragments and 1.25 KB of loads per 12 MFMAs and wave, of 128 bytes a clock), and
+// by the length of the K loop when it is not, which smaller tiles shorten: one
+// 64-wide slice takes 0.23 us on 64 x 64 tiles, 0.50 on 64 x 128, 0.59 on 128 x 128,
+// 0.68 on 128 x 192 with a work-group per CU.  The schedule inside a slice, the MFMAs
+// and their k order are those of gemm_bf16_big_kernel: the same bits.
+//   1200 x 4608 x 1152 + GELU 46 -> 21 us, 300 x 1152 x 1152 + residual 38 -> 7.6,
+// 2500 x 1152 x 4608 106 -> 51, 13600 x 1152 x 1152 65 -> 48 (256 x 128 or 256 x 192
+// tiles before).  Slices of 32 (256 x 128 and 128 x 256 tiles, two work-groups per
+// CU): 284 us against 239 for 128 x 192 tiles and 64-wide slices at 32768 x 3456 x 1152.
+template <int EPI, bool KEEP, int TM, int TN, int NS, int OCC>
+__global__ __launch_bounds__(NTHR, OCC) void gemm_bf16_dma_kernel(
+    const bf16* __restrict__ A, const bf16* __restrict__ W, const bf16* __restrict__ bias,
+    const float* resid, void* out, bf16* keep_out, int M, int N, int K, int n_ntiles, int n_tiles,
+    RowSwap rs) {
+  constexpr int BMT = 64 * TM, BNB = 64 * TN;
+  constexpr int STAGE = (BMT + BNB) * BK;  // elements of one K slice of both operands
+  // the slices' buffers, and after them the epilogue's staged rows
+  constexpr int EPI_ELEMS = epilogue_elems<EPI, KEEP, TM, TN>();
+  constexpr int LDS_ELEMS = NS * STAGE > EPI_ELEMS ? NS * STAGE : EPI_ELEMS;
+  __shared__ __attribute__((aligned(1024))) bf16 lds[LDS_ELEMS];
+
+  // tile order: contiguous ranges per XCD, then groups of BIG_GROUP m-tiles
+  // with m fastest, so that the A and W slices of the tiles running together
+  // on one XCD fit its L2
+  uint32_t bid = blockIdx.x;
+  {
+    const uint32_t per = (uint32_t)n_tiles >> 3, extra = (uint32_t)n_tiles & 7u, xcd = bid & 7u;
+    bid = xcd * per + min(xcd, extra) + (bid >> 3);
+  }
+  const int n_mt = n_tiles / n_ntiles;
+  constexpr int GROUP = BIG_GROUP * 256 / BMT;  // m-tiles of 1024 rows
+  const int per_group = GROUP * n_ntiles;
+  const int grp = (int)bid / per_group;
+  const int first_m = grp * GROUP;
+  const int gm = min(GROUP, n_mt - first_m);
+  const int rem = (int)bid - grp * per_group;
+  const int m0 = (first_m + rem % gm) * BMT, n0 = (rem / gm) * BNB;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int l32 = lane & 31, g = lane >> 5;
+
+  // Loader: one instruction moves 64 16-byte chunks (8 rows of a slice) straight
+  // into LDS, lane after lane.  Rows lie unpadded (128 bytes); lane (r, p) of a
+  // group of 8 rows fetches logical chunk p ^ r, so that a column of chunks is
+  // spread over all banks when fragments read it.  Rows past the end re-read the
+  // last one: they only enter outputs that are not stored.
+  constexpr int A_LOADS = BMT / 32, W_LOADS = BNB / 32, NL = A_LOADS + W_LOADS;
+  const uint32_t row_bytes = (uint32_t)K * 2u;
+  const int a_rows = min(BMT, M - m0), w_rows = min(BNB, N - n0);
+  const u32x4 ra = dma_rsrc(A + (int64_t)m0 * K, (uint32_t)a_rows * row_bytes);
+  const u32x4 rw = dma_rsrc(W + (int64_t)n0 * K, (uint32_t)w_rows * row_bytes);
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16*)lds + (uint32_t)wave * 1024u);
+  uint32_t goff[NL];
+  {
+    const int r = lane >> 3, ch = (lane & 7) ^ r;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int row = 8 * (wave + 4 * (i < A_LOADS ? i : i - A_LOADS)) + r;
+      goff[i] = (uint32_t)min(row, (i < A_LOADS ? a_rows : w_rows) - 1) * row_bytes + (uint32_t)ch * 16u;
+    }
+  }
+  // load i of slice kt into LDS buffer buf
+  auto dma = [&](int i, int kt, int buf) {
+    const uint32_t at = lds0 + (uint32_t)buf * (STAGE * 2) + (i < A_LOADS ? i * 4096 : BMT * BK * 2 + (i - A_LOADS) * 4096);
+    dma_b128(i < A_LOADS ? ra : rw, goff[i], (uint32_t)kt * (BK * 2), at);
+  };
+
+  floatx16 acc[TN][TM];
+#pragma unroll
+  for (int a = 0; a < TN; ++a)
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+  bf16x8 af[2][TM], wf[2][TN];
+  auto fread = [&](int slot, int buf, int ks) {
+    const bf16* As = lds + buf * STAGE + l32 * BK + (((2 * ks + g) ^ (l32 & 7)) * 8);
+    const bf16* Ws = As + BMT * BK;
+#pragma unroll
+    for (int b = 0; b < TM; ++b) af[slot][b] = *reinterpret_cast<const bf16x8*>(As + (wm * TM + b) * 32 * BK);
+#pragma unroll
+    for (int a = 0; a < TN; ++a) wf[slot][a] = *reinterpret_cast<const bf16x8*>(Ws + (wn * TN + a) * 32 * BK);
+  };
+
+  // One K slice from LDS buffer `buf`.  MORE: slice kt + 1 exists; before the last
+  // 16-wide step the wave waits until its loads of that slice have landed
+  // (LEFT slices after it may still be in flight) and until its own fragment
+  // reads of this slice have returned; behind the barrier the next slice is
+  // whole and this one's buffer is free.  LD: slice kt + NS goes there.
+  auto slice = [&](int kt, int buf, auto more_c, auto left_c, auto ld_c) {
+    constexpr bool MORE = decltype(more_c)::value, LD = decltype(ld_c)::value;
+    constexpr int LEFT = decltype(left_c)::value, NMF = TM * TN;
+    const int nbuf = buf + 1 == NS ? 0 : buf + 1;
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      const int cur = ks & 1;
+      if (ks + 1 < BK / 16) {
+        fread(cur ^ 1, buf, ks + 1);
+      } else if (MORE) {
+        wait_barrier<LEFT * NL>();
+        fread(cur ^ 1, nbuf, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < NMF; ++j) {
+        const int a = j / TM, bb = j % TM;
+        acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[cur][a], af[cur][bb], acc[a][bb], 0, 0, 0);
+        if (LD && ks + 1 == BK / 16) {
+#pragma unroll
+          for (int i = j * NL / NMF; i < (j + 1) * NL / NMF; ++i) dma(i, kt + NS, buf);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+
+  const int nk = K / BK;
+  for (int t = 0; t < min(NS, nk); ++t)
+#pragma unroll
+    for (int i = 0; i < NL; ++i) dma(i, t, t);
+  // slice 0 landed: at most min(NS, nk) - 1 later ones in flight
+  if (nk >= NS)
+    wait_barrier<(NS - 1) * NL>();
+  else
+    wait_barrier<0>();
+  fread(0, 0, 0);
+  using yes = std::true_type;
+  using no = std::false_type;
+  int kt = 0, buf = 0;
+  for (; kt + NS < nk; ++kt) {
+    slice(kt, buf, yes{}, std::integral_constant<int, NS - 2>{}, yes{});
+    buf = buf + 1 == NS ? 0 : buf + 1;
+  }
+  // the last NS slices: nothing more to load (and all of it was issued NS - 1
+  // slices ago: no need to count)
+  for (; kt + 1 < nk; ++kt) {
+    slice(kt, buf, yes{}, std::integral_constant<int, 0>{}, no{});
+    buf = buf + 1 == NS ? 0 : buf + 1;
+  }
+  tile_epilogue<EPI, KEEP, TM, TN, LDS_ELEMS>(acc, lds, bias, resid, out, keep_out, M, N, m0, n0, rs, [&] {
+    slice(kt, buf, no{}, std::integral_constant<int, 0>{}, no{});
+  });
 }
 
 // bf16 transposes of up to kMaxTranspose matrices in one launch (the weights
