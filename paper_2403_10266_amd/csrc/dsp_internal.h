@@ -185,6 +185,9 @@ extern "C" int dsp_choice_attn_bwd(int D, int64_t bx, int H, int Hkv, int64_t L,
 //   Output tile of the bf16 GEMM, rows << 16 | columns (| 1 << 31: four K slices in
 // flight where two are usual), for the plain GELU epilogue or another.
 extern "C" uint32_t dsp_choice_linear(int64_t M, int64_t N, int64_t K, int gelu);
+//   Output tile of the bf16 weight gradient of M tokens (its output: N x K) in the same
+// form, and the parts its reduction is cut into with the workspace it asks for.
+extern "C" uint32_t dsp_choice_weight_grad(int64_t M, int64_t N, int64_t K, int* splits);
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? DSP_OK : DSP_ERR_HIP; }
 inline int last_launch_status() { return hip_status(hipGetLastError()); }

@@ -281,11 +281,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float4* __rest
 // 1024 / G rows at a time, eight loads of each thread in flight.  The rows' sums
 // then meet in a fixed tree (lanes, then waves in order): deterministic, and a
 // shorter chain of fp32 adds than a walk down the column.
-//   13600 bf16 rows of 1152 / 3456 / 4608 columns: 24 / 25 / 31 us with four loads in
-// flight, about 6 less with eight (1.3 / 3.7 /
-// 4.0 TB/s), where one thread walking down 4 columns (two to five work-groups on
-// the chip, one load in flight each) took 3750 / 3720 / 3570 us; 2048 fp32 rows
-// 470 -> 5-11 us.
+//   13600 bf16 rows of 1152 / 3456 / 4608 columns: @@
+// where one thread walking down 4 columns (two to five work-groups on the chip, one
+// load in flight each) took 3750 / 3720 / 3570 us; 2048 fp32 rows 470 -> 5-11 us.
 constexpr int CS_THREADS = 1024, CS_UNROLL = 8;
 
 template <bool BF, int G>
@@ -573,7 +571,8 @@ __global__ __launch_bounds__(GNTHR, OCC) void gemm_grad_tt_dma_kernel(GradArgs p
 // splits work-groups takes full rounds of 256 * levels and one of the rest, with
 // 1 .. levels of them per CU; a round with j per CU takes a[j - 1] + b[j - 1] * (64-row
 // slices) microseconds, and each partial of the reduction a write and a read at
-// about 4 TB/s each.  Values from the shapes named at the kernel.
+// about 4 TB/s each.  Estimates, not a fit: slopes scaled from the forward tiles (same
+// schedule) and checked on the shapes named at the kernel; @@
 struct GradTile {
   int tm, tn, levels;
   double a[3], b[3];
@@ -691,9 +690,11 @@ int launch_colsum_f32(const float* dy, float* db, int64_t M, int N, hipStream_t 
 }
 
 // The partials a caller's workspace provides for (the launch takes as many as it
-// needs of them): the split count minimising rounds of work-groups times slices per
-// split plus the extra partials' write and read, with at least 32 slices per split
-// (so a reduction of fewer than 4096 runs without a workspace).
+// needs of them; choose_grad decides): the split count minimising rounds of work-groups
+// of 256-row tiles times slices per split plus the extra partials' write and read,
+// with at least 32 slices in each split but the last, so that a reduction of at most 63 x
+// 64 - 64 = 3968 runs without a workspace.  The size is part of the interface: callers
+// allocate it, and programs that stored it must find it enough.
 int grad_splits(int64_t M, int64_t N, int64_t K) {
   const bool big = M >= 512 && N >= 512 && M % 8 == 0 && N % 8 == 0 && K >= 2048 &&
                    (int64_t)GBK * M * 2 < (int64_t(1) << 31) && (int64_t)GBK * N * 2 < (int64_t(1) << 31) &&
@@ -716,6 +717,13 @@ int grad_splits(int64_t M, int64_t N, int64_t K) {
     }
   }
   return best;
+}
+
+extern "C" uint32_t dsp_choice_weight_grad(int64_t M, int64_t N, int64_t K, int* splits) {
+  const GradChoice c = choose_grad(N, K, M, grad_splits(N, K, M));
+  *splits = c.splits;
+  const GradTile& t = kGradTiles[c.tile];
+  return (uint32_t)(64 * t.tm << 16 | 64 * t.tn) | (c.tile == 2 ? 1u << 31 : 0u);
 }
 
 bool grad_gemm_fits(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {

@@ -1,6 +1,8 @@
-"""The bf16 GEMM's pipelined tiles against float64: every tile shape (64 x 64, 64 x 128,
-128 x 128 with two and four K slices in flight, 128 x 192), fewer K slices than
-buffers, partial tiles on both sides, and each epilogue.
+"""The bf16 GEMM's tiles against float64: every tile shape (64 x 64 and 128 x 128 with four
+K slices in flight, 64 x 128, 128 x 128 and 128 x 192 with two, the register-staged 256-row
+tiles), as many, fewer and more K slices than buffers, partial tiles on both sides, and
+each epilogue.  Each case names its tile (rows, columns, four slices in flight) and
+asserts that the launch takes it; one tile for the plain GELU where two are named.
 
 Bound per output: fp32 accumulation of K bf16 products is off by at most
 (K + 4) 2^-24 sum |a| |w| (bias and residual included in the sum), the GELU
@@ -11,8 +13,13 @@ import pytest
 import synth
 from tests.gpu_util import say
 from tests.test_gpu_block_bwd import _train_case
+from tests.test_launch_choices_cpu import linear
 
 pytestmark = pytest.mark.gpu
+
+
+T64x64, T64x128 = (64, 64, False), (64, 128, False)   # (64 x 64 always has four slices in flight)
+T128x128, T128x128_DEEP, T128x192 = (128, 128, False), (128, 128, True), (128, 192, False)
 
 
 @pytest.fixture(scope="module")
@@ -22,15 +29,22 @@ def torch():
 
 
 @pytest.mark.parametrize("epi", ["none", "gelu", "relu", "resid", "f32"])
-@pytest.mark.parametrize("M,N,K", [
-    (1, 8, 64), (63, 72, 128), (65, 200, 192), (100, 64, 256), (130, 1160, 320),   # 64 x 64: 1 to 5 slices, 4 buffers
-    (1201, 4600, 1152),     # 64 x 128
-    (2500, 1152, 192),      # 128 x 128, four slices in flight, three slices
-    (4501, 3464, 1152),     # 128 x 128, two work-groups per CU
-    (8001, 1160, 1152),     # 128 x 192
+@pytest.mark.parametrize("M,N,K,tile,gelu_tile", [
+    (1, 8, 64, T64x128, None), (63, 72, 128, T64x128, None), (65, 200, 192, T64x128, None),     # 1 to 5 slices, 2 buffers
+    (100, 64, 256, T64x128, None), (130, 1160, 320, T64x128, None), (770, 4664, 448, T64x128, None),
+    (8451, 136, 64, T64x64, None), (8668, 152, 128, T64x64, None), (8918, 144, 192, T64x64, None),  # 1 to 5, 4 buffers
+    (8246, 144, 256, T64x64, None), (8373, 160, 320, T64x64, None), (65, 200, 448, T64x64, None),
+    (513, 1160, 1152, T64x64, None),
+    (2500, 1152, 192, T128x128, T64x128), (8268, 656, 192, T128x128, None), (4501, 3464, 1152, T128x128, None),
+    (2001, 1160, 4608, T128x128_DEEP, None), (385, 4712, 4608, T128x128_DEEP, None),
+    (9092, 1288, 64, T128x192, None), (6569, 1160, 320, T128x192, None), (1201, 4600, 1152, T128x192, None),
+    (8001, 1160, 1152, T128x192, None),
+    (8159, 1448, 4608, (256, 192, False), None), (3974, 3856, 1152, (256, 256, False), None),
+    (100, 104, 72, (256, 128, False), None),
 ])
-def test_gemm_tiles(torch, M, N, K, epi):
+def test_gemm_tiles(torch, M, N, K, tile, gelu_tile, epi):
     import paper_2403_10266_amd as dsp
+    assert linear(M, N, K, epi == "gelu") == (gelu_tile if gelu_tile and epi == "gelu" else tile)
     gen = torch.Generator(device="cuda:0").manual_seed(M + N + K)
 
     def draw(*s):
@@ -60,9 +74,18 @@ def test_gemm_tiles(torch, M, N, K, epi):
 @pytest.mark.parametrize("flags,T,S", [(0, 3, 10), (4, 5, 40)])
 def test_block_train_small_tiles(torch, flags, T, S):
     """Few tokens at widths that are multiples of 64: the training epilogues (kept
-    derivative, its use in the backward) on 64-row tiles."""
+    pre-activation, its use in the backward) on 64-row tiles."""
     w = synth.Workload("block_64", "block", "bf16", B=2, T=T, S=S, C=128, H=2, F=256, seed=31)
     _train_case(torch, w, True, flags)
+
+
+def test_block_train_kept_derivative_small_tiles(torch):
+    """Tokens that fill every CU with 256-row tiles at a width of 64: GELU' is kept, and
+    both it and its use in the backward run on 64-row tiles."""
+    w = synth.Workload("block_kept", "block", "bf16", B=1, T=37, S=260, C=64, H=2, F=1160, seed=32)
+    tokens = w.B * w.T * w.S
+    assert -(-tokens // 256) * -(-w.F // 192) >= 256 and linear(tokens, w.F, w.C) == T64x128
+    _train_case(torch, w, True, 0)
 
 
 @pytest.mark.parametrize("offset", [1, 2, 3])

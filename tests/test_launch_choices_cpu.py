@@ -76,6 +76,27 @@ def linear(M, N, K, gelu=False):
     return (v >> 16) & 0x7FFF, v & 0xFFFF, bool(v >> 31)
 
 
+def weight_grad(M, N, K):
+    """((rows, columns, whether four slices are in flight) of the output tile, splits)"""
+    f = dsp.lib().dsp_choice_weight_grad
+    splits = INT()
+    f.restype, f.argtypes = ctypes.c_uint32, [I64, I64, I64, ctypes.POINTER(INT)]
+    v = f(M, N, K, ctypes.byref(splits))
+    return ((v >> 16) & 0x7FFF, v & 0xFFFF, bool(v >> 31)), splits.value
+
+
+def test_weight_gradient_workspace():
+    """No workspace, and no split, up to 3968 tokens; at most what the workspace holds past it."""
+    ws = dsp.lib().dsp_linear_bwd_weight_workspace_bytes
+    for N, K in ((1152, 1152), (576, 4608), (8, 8)):
+        assert ws(3968, N, K, dsp.DSP_BF16) == 0 and weight_grad(3968, N, K)[1] == 1
+    assert ws(3969, 1152, 1152, dsp.DSP_BF16) > 0
+    for M in (3969, 5001, 13600, 32768):
+        for N, K in ((1152, 1152), (3456, 1152), (1152, 4608), (640, 72)):
+            need = ws(M, N, K, dsp.DSP_BF16)
+            assert weight_grad(M, N, K)[1] <= max(1, need // (4 * N * K))
+
+
 @pytest.mark.parametrize("N", [8, 64, 136, 1152])
 @pytest.mark.parametrize("K", [64, 1024])
 def test_linear_grid(N, K):
