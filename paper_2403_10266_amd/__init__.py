@@ -158,10 +158,12 @@ class _on:
     def __init__(self, stream):
         torch = _torch()
         if stream is None:
-            # the handle alone: building a torch.cuda.Stream object costs 2.6 us,
-            # a sixth of a small call's host time
+            # the handle alone where torch offers it (an internal function): building a
+            # torch.cuda.Stream object costs 2.6 us, a sixth of a small call's host time
             self.guard = None
-            self.handle = torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+            device = torch.cuda.current_device()
+            raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            self.handle = raw(device) if raw else torch.cuda.current_stream(device).cuda_stream
         else:
             self.guard = torch.cuda.stream(stream)
             self.handle = stream.cuda_stream

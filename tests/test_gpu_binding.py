@@ -95,3 +95,21 @@ def test_explicit_stream(torch, dsp):
     assert np.array_equal(bits16(y), bits16(base))
     want = oracle.spatial_attention(*(host(t) for t in (q, k, v)), 2)
     assert_close(host(o), want, "bf16", "attention on a side stream")
+
+
+def test_current_stream_without_the_internal_handle(torch, dsp, monkeypatch):
+    """Without torch's internal function for the raw handle, calls still run on the
+    current stream: captured there, the launch is replayed."""
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    x = torch.arange(2 * 4 * 8 * 8, device="cuda").to(torch.float32).view(2, 4, 8, 8)
+    y = torch.empty_like(x).view(-1)
+    dsp.dsp_switch(x, 1, 2, 1, out=y)
+    want = y.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        dsp.dsp_switch(x, 1, 2, 1, out=y)
+    for _ in range(3):
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
