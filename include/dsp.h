@@ -249,7 +249,7 @@ int dsp_attn_fwd_lse(const void* q, const void* k, const void* v, void* o, float
  *   multiples of 8 (DSP_ERR_ALIGN); 64 * qkv_strides[2] * 2 and
  *   64 * o_strides[2] * 2 below 2^31 (DSP_ERR_SHAPE).  Deterministic: no
  *   atomics, so repeated calls give identical bits.
- * dtype DSP_F32: fp32 FMA throughout; 1 <= D <= 256.
+ * dtype DSP_F32: fp32 products and accumulation throughout; 1 <= D <= 256.
  * scale <= 0 selects 1/sqrt(D).  An empty input launches nothing.
  * Errors: DSP_ERR_NULL, DSP_ERR_SHAPE, DSP_ERR_DTYPE, DSP_ERR_ALIGN,
  *   DSP_ERR_ARG (scale not finite, overlapping gradient rows), DSP_ERR_HIP.
@@ -350,7 +350,8 @@ int dsp_layernorm_bwd(const void* x, int x_dtype, const void* dy, int dy_dtype, 
  *           (out = residual + a*W + bias).
  * epilogue: DSP_EPI_NONE, DSP_EPI_GELU (erf GELU: x*Phi(x)), DSP_EPI_RESID,
  *           DSP_EPI_F32, DSP_EPI_RELU (max(0, x): the FFN activation of Eq. 5).
- * dtype:    DSP_BF16 (bf16 MFMA, fp32 accumulation) or DSP_F32 (fp32 FMA).
+ * dtype:    DSP_BF16 (bf16 MFMA, fp32 accumulation) or DSP_F32 (fp32
+ *           products and accumulation).
  * bf16 needs K % 8 == 0 and 16-byte aligned a, w, out and residual
  * (DSP_ERR_ALIGN).  out must not overlap a, w or bias.
  * Errors: DSP_ERR_NULL, DSP_ERR_SHAPE (M < 0, N < 1, K < 1), DSP_ERR_DTYPE,
@@ -383,7 +384,7 @@ int dsp_linear(const void* a, const void* w, const void* bias, const float* resi
  *   deterministic.
  * dtype DSP_BF16: bf16 operands on the matrix cores, fp32 accumulation;
  *   N % 8 == 0 and K % 8 == 0 and 16-byte aligned tensors (DSP_ERR_ALIGN).
- * dtype DSP_F32: fp32 FMA.
+ * dtype DSP_F32: fp32 products and accumulation.
  * All pointers are DEVICE pointers owned by the caller; outputs must not
  * overlap inputs (DSP_ERR_ARG).  M == 0: dsp_linear_bwd_data launches
  * nothing; dsp_linear_bwd_weight writes dw = 0 (and db = 0).

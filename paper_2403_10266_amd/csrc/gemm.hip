@@ -2,12 +2,15 @@
 // projections, Eq. 5 FFN W_1 and W_2): out = epilogue(a * W + bias) with a
 // [M, K] row-major and W stored [N][K] (reduction index contiguous).
 //
-// bf16 path (gfx950 MFMA):
-//  * 256 x 128 output tile per work-group, 4 waves of 128 x 64, K staged 64 at
-//    a time through LDS (row pitch 144 bytes, an odd multiple of 16: the
-//    16-byte fragment reads of 16 consecutive rows hit distinct banks), with
-//    the next K slice prefetched into registers during the current slice's
-//    MFMAs.
+// bf16 path (gfx950 MFMA), three kernels over output tiles; choose_tiles picks by cost:
+//  * gemm_bf16_dma_kernel: 64 x 64 to 128 x 192 tiles, K slices straight from memory into
+//    a ring of LDS buffers.  Most launches, any size with K % 64 == 0 and N % 8 == 0.
+//  * gemm_bf16_big_kernel: 256 x 256 or 256 x 192 tiles staged through registers, for many
+//    full rounds with a long K, and for large launches whose K is not a multiple of 64.
+//  * gemm_bf16_kernel, the fallback for everything else: 256 x 128 tiles, 4 waves of 128 x
+//    64, K staged 64 at a time through LDS (row pitch 144 bytes, an odd multiple of 16:
+//    the 16-byte fragment reads of 16 consecutive rows hit distinct banks), with
+//    the next K slice prefetched into registers during the current slice's MFMAs.
 //  * v_mfma_f32_32x32x16_bf16 with the operands swapped (W rows on the MFMA
 //    M side, activation rows on the N side), so each lane ends up owning one
 //    output row and four consecutive output columns per register group: the
@@ -340,7 +343,7 @@ template <int EPI, bool KEEP, int TM, int TN>
 constexpr int epilogue_elems() {
   constexpr int BMT = 64 * TM, BNB = 64 * TN;
   if (epi_is_bwd<EPI>() || EPI == DSP_EPI_RESID || EPI == DSP_EPI_F32)
-    return BMT / (TM == 4 && TN == 4 && EPI != DSP_EPI_F32 ? 4 : TM >= 2 ? 2 : 1) * (BNB + 4) * 2 + 2 * BMT;
+    return BMT / (TM >= 2 ? 2 : 1) * (BNB + 4) * 2 + 2 * BMT;
   return BMT * (BNB + 8) * (KEEP && TM == 1 ? 2 : 1) + 2 * BMT;
 }
 
@@ -722,11 +725,11 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_bf16_big_kernel(
 // both operands go from memory straight into a ring of NS LDS buffers, up to NS
 // slices in flight, and OCC work-groups share a CU, so one's epilogue and
 // barriers run under the other's MFMAs.  It needs no registers for the loads.
-// Bound by LDS bandwidth once the chip is full (128 x 192 tiles: 2.5 KB of
-// fragments and 1.25 KB of loads per 12 MFMAs and wave, of 128 bytes a clock), and
-// by the length of the K loop when it is not, which smaller tiles shorten: one
-// 64-wide slice takes 0.23 us on 64 x 64 tiles, 0.50 on 64 x 128, 0.59 on 128 x 128,
-// 0.68 on 128 x 192 with a work-group per CU.  The schedule inside a slice, the MFMAs
+// On a full chip no one unit is (13600 x 1152 x 1152 + residual, 128 x 128 tiles: matrix cores
+// busy 31%, LDS fragment reads 33%, waves waiting 36%; the register-staged 256 x 192 tiles
+// at 32768 x 1152 x 4608: 53%, 33% and 20%); otherwise the length of the K loop decides, which
+// smaller tiles shorten: one 64-wide slice takes 0.23 us on 64 x 64 tiles, 0.50 on 64 x 128,
+// 0.59 on 128 x 128, 0.68 on 128 x 192 with a work-group per CU.  The schedule inside a slice, the MFMAs
 // and their k order are those of gemm_bf16_big_kernel: the same bits.
 //   1200 x 4608 x 1152 + GELU 46 -> 21 us, 300 x 1152 x 1152 + residual 38 -> 7.6,
 // 2500 x 1152 x 4608 106 -> 51, 13600 x 1152 x 1152 65 -> 48 (256 x 128 or 256 x 192
@@ -859,8 +862,9 @@ __global__ __launch_bounds__(NTHR, OCC) void gemm_bf16_dma_kernel(
     slice(kt, buf, yes{}, std::integral_constant<int, NS - 2>{}, yes{});
     buf = buf + 1 == NS ? 0 : buf + 1;
   }
-  // the last NS slices: nothing more to load (and all of it was issued NS - 1
-  // slices ago: no need to count)
+  // the last NS slices: nothing more to load, and each waits for all that is in flight
+  // (with NS = 2 that is the next slice; with 4 the first of these waits sooner than
+  // its own slice needs)
   for (; kt + 1 < nk; ++kt) {
     slice(kt, buf, yes{}, std::integral_constant<int, 0>{}, no{});
     buf = buf + 1 == NS ? 0 : buf + 1;
@@ -945,7 +949,7 @@ int launch_transpose_bf16_batch(const void* const* x, void* const* y, const int6
 // stands alone, with two it runs under the other's MFMAs.  The register-staged 256 x
 // 256 and 256 x 192 tiles win where many full rounds meet a long K (8000 x 2048 x
 // 8192: 220 against 256 us), the 128-row tiles below that and with GELU (32768 x 4608 x
-// 1152: 365 against 396 us).
+// 1152: 365 against 396 us alone; inside a block forward the gain is within the runs' noise).
 enum { T_BIG256 = 0, T_BIG192, T_128x192, T_128x128, T_128x128_DEEP, T_64x128, T_64x64, T_COUNT };
 struct TileShape {
   int bm, bn, levels;
