@@ -342,8 +342,8 @@ __global__ __launch_bounds__(CS_THREADS) void colsum_kernel(const void* __restri
 
 // A few rows: one thread per 16-byte chunk (bf16) or column (fp32).  The tree of a
 // 1024-thread work-group takes longer than the rows do (8 fp32 rows of 64 columns with
-// their weight gradient 6.6 against 7.8 us).
-constexpr int kFewRows = 16;
+// their weight gradient 6.6 against 7.8 us; 16 bf16 rows of 8192 24.2 against 21.0).
+constexpr int kFewRows = 8;
 template <bool BF>
 __global__ __launch_bounds__(256) void colsum_few_kernel(const void* __restrict__ dyp, float* db, int M, int N) {
   constexpr int V = BF ? 8 : 1;

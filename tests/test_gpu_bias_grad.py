@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("M,N", [(1, 8), (9, 1160), (16, 4104), (17, 40), (63, 24), (64, 16), (257, 40), (512, 1152), (2047, 1160), (2049, 128),
+@pytest.mark.parametrize("M,N", [(1, 8), (8, 1160), (9, 1160), (16, 4104), (17, 40), (63, 24), (64, 16), (257, 40), (512, 1152), (2047, 1160), (2049, 128),
                                  (4100, 4096), (5000, 4104)])
 def test_bias_gradient(dtype, M, N):
     import paper_2403_10266_amd as dsp
